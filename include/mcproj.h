@@ -88,7 +88,8 @@ typedef struct {
   double alpha;               /* step scale (Alg. 2 alpha), default 1                           */
   double lambda;              /* damping (Alg. 2 lambda), >= 0, default 0                       */
   double max_step;            /* > 0: DIVERGED when ||alpha * step|| > max_step; <= 0: off       */
-  double fp64_cond_threshold; /* FP32 mode: when the FP32 Cholesky of J J^T fails or its
+  double fp64_cond_threshold; /* FP32 mode: when the FP32 Cholesky of J J^T (the rows in the basis
+                                 the family's kernel forms them in) fails or its
                                  condition estimate (max L_ii / min L_ii)^2 exceeds this (1e6),
                                  the step is redone in FP64 and that configuration takes FP64
                                  steps until it terminates                                     */
@@ -100,9 +101,7 @@ typedef struct {
                                  2 fused (persistent work-queue kernel over the whole batch)     */
   int32_t waves_per_block;    /* fused variant: 1, 2 or 4 wavefronts per workgroup (0 = auto)   */
   int32_t blocks_per_cu;      /* fused variant: resident workgroups per CU for the persistent
-                                 grid (0 = auto; with auto, a stacked-mode batch larger than the
-                                 lanes of the one-wave-per-SIMD launch of the 36-DoF family runs
-                                 in its two-waves-per-SIMD build, same results)                  */
+                                 grid (0 = auto: as many as fit)                               */
   int32_t mode;               /* 0 stacked: one min-norm step on all constraint rows together;
                                  1 cyclic (Sec. IV-C, Alg. 2 getDescentStep): one min-norm step
                                  per constraint block, in the scene's block order, each from the
@@ -321,9 +320,12 @@ mc_status extend_batch(const mc_problem* p, int64_t E, const void* q_start, cons
                        int32_t* particle, int32_t* n_points, void* stream);
 
 /* mc_eval_condition — diagnostic: the condition estimate that decides the FP32 -> FP64 switch,
-   kappa_est = (max L_ii / min L_ii)^2 of the Cholesky factor of J J^T + lambda I, computed as the
-   projection kernels compute it (MC_F32: FP32 Jacobian columns, Gram and factorisation; MC_F64:
-   FP64), or +inf where the factorisation fails. q [d][ld] and kappa [n] are of dtype. */
+   kappa_est = (max L_ii / min L_ii)^2 of the Cholesky factor of J J^T + lambda I on the scene's rows
+   (MC_F32: FP32 Jacobian columns, Gram and factorisation; MC_F64: FP64), or +inf where the
+   factorisation fails. The kernels of the dual-arm and 36-DoF families take the estimate in the rows
+   they work in, each pose block's body twist, which are these turned by the pose and, in the angular
+   rows, multiplied by an inverse SO(3) Jacobian: the same singular values up to that factor (1 at a
+   zero rotation error). q [d][ld] and kappa [n] are of dtype. */
 mc_status mc_eval_condition(const mc_problem* p, int64_t n, const void* q, int64_t ld, mc_dtype dtype,
                             double lambda, void* kappa, void* stream);
 

@@ -11,7 +11,7 @@
 #include <vector>
 
 #include "../../include/mcproj.h"
-#include "kin.hpp"
+#include "leaf.hpp"
 #include "ops.hpp"
 
 using namespace mc;
@@ -303,16 +303,59 @@ struct HBounds {
   double lo[3], hi[3];
 };
 
+// Joints of a family's leaf-to-root walk by slot (-1: none), and whether its joint origins are rotated.
+struct WalkOrder {
+  std::vector<int> slot;
+  bool rot = false;
+};
+template <class Topo>
+WalkOrder walk_order_of() {
+  static_assert(2 * Topo::NG <= MAXW, "walk longer than the constants' table");
+  WalkOrder w;
+  for (int g = 0; g < Topo::NG; ++g)
+    for (int k = 0; k < 2; ++k) w.slot.push_back(Topo::walk[g][k]);
+  w.rot = Topo::origin_rot;
+  return w;
+}
+WalkOrder walk_order(int family) {
+  switch (family) {
+    case MC_FAMILY_DUAL14_REL: return walk_order_of<TopoDual14Rel>();
+    case MC_FAMILY_HUMANOID36: return walk_order_of<TopoHumanoid36>();
+    case MC_FAMILY_DIGIT36: return walk_order_of<TopoDigit36>();
+  }
+  return {};
+}
+
 template <class T>
 void fill_tp(TP<T>& t, const HScene& s, const std::vector<HT>& tref, const std::vector<double>& submass, double Mtot,
              const HBounds& hb) {
   std::memset(&t, 0, sizeof(TP<T>));
+  const WalkOrder order = walk_order(s.family);
   for (size_t j = 0; j < s.joints.size() && j < MAXJ; ++j) {
     for (int k = 0; k < 9; ++k) t.jR[j][k] = T(s.joints[j].R[k]);
     for (int k = 0; k < 3; ++k) t.jp[j][k] = T(s.joints[j].p[k]);
     t.mass[j] = T(s.mass[j]);
     for (int k = 0; k < 3; ++k) t.mcom[j][k] = T(s.mass[j] * s.com[j][k]);
     t.submass[j] = T(submass[j]);
+  }
+  for (size_t w = 0; w < order.slot.size(); ++w) {
+    const int j = order.slot[w];
+    if (j < 0) continue;
+    const HJoint& J = s.joints[j];
+    const bool rot = order.rot;
+    T* c = t.jc + w * (rot ? 16 : 8);
+    for (int k = 0; k < 3; ++k) c[k] = T(J.p[k]);
+    if (rot) {
+      for (int k = 0; k < 9; ++k) c[3 + k] = T(J.R[k]);
+    } else {
+      for (int k = 0; k < 3; ++k) {
+        double h = s.mass[j] * s.com[j][k];
+        for (size_t i = 0; i < s.joints.size(); ++i)
+          if (s.joints[i].parent == j) h += submass[i] * s.joints[i].p[k];
+        c[3 + k] = T(h);
+      }
+      c[6] = T(submass[j]);
+    }
   }
   for (size_t f = 0; f < s.frames.size() && f < MAXF; ++f) {
     for (int k = 0; k < 9; ++k) t.fR[f][k] = T(s.frames[f].R[k]);
@@ -770,7 +813,6 @@ struct mc_problem {
   // resident workgroups per CU of the persistent kernel, by (FP64 mode, waves per block = 1, 2, 4);
   // queried once, so later calls (and calls under stream capture) make no runtime query
   mutable int occ[2][3] = {{0, 0, 0}, {0, 0, 0}};
-  mutable int occ_wide = 0;  // resident 256-thread workgroups per CU of the two-wave launch
   // launch shape stored by mc_autotune_project, by (FP64 mode, cyclic mode); waves_per_block 0 = none
   mc_launch_shape tuned[2][2] = {{{0, 0, 0}, {0, 0, 0}}, {{0, 0, 0}, {0, 0, 0}}};
   // mc_set_check_lanes: lanes per configuration of the exact-check tail (0: by queue length)
@@ -1043,8 +1085,6 @@ mc_status mc_problem_create(const void* blob, size_t nbytes, mc_problem** out) {
   return MC_OK;
 }
 
-static bool lds_ok(const mc_problem* p, size_t bytes) { return bytes <= p->max_lds_per_block; }
-
 static mc_status check_opts(const mc_problem* p, const mc_project_opts* o) {
   if (!o) return fail(MC_ERR_INVALID_ARG, "null opts");
   if (o->dtype != MC_F32 && o->dtype != MC_F64) return fail(MC_ERR_INVALID_ARG, "bad dtype");
@@ -1198,28 +1238,18 @@ static mc_status project_impl(const mc_problem* p, int64_t n, const void* q_in, 
       wpb = ts.waves_per_block;
       bpc = ts.blocks_per_cu;
     }
-    while (wpb > 1 && (cyc ? 2 : 1) * ops->lds_bytes(64 * wpb) > p->max_lds_per_block) wpb >>= 1;
+    while (wpb > 1 && ops->lds_bytes(64 * wpb, cyc ? 1 : 0) > p->max_lds_per_block) wpb >>= 1;
     const int block = 64 * wpb;
-    const int bpc_req = bpc;  // 0: occupancy limit (and the two-wave build for large batches)
     if (bpc <= 0) {
       int& c = p->occ[ops->f64][wpb == 1 ? 0 : wpb == 2 ? 1 : 2];
       if (c <= 0) c = ops->persistent_blocks_per_cu(block);  // registers bound it, not LDS
       bpc = c;
     }
     int64_t grid = int64_t(p->n_cu) * bpc;
-    // a batch beyond the lanes of the one-wave launch, with the launch shape left to the library:
-    // the two-wave launch where the family has one
-    const bool wide = !cyc && ops->project_persistent_wide != nullptr && bpc_req == 0 &&
-                      n > grid * block && lds_ok(p, ops->lds_bytes(256));
-    if (wide) {
-      if (p->occ_wide <= 0) p->occ_wide = ops->persistent_wide_blocks_per_cu();
-      grid = int64_t(p->n_cu) * p->occ_wide;
-    }
-    const int lblock = wide ? 256 : block;
-    grid = std::min<int64_t>(grid, (n + lblock - 1) / lblock);
+    grid = std::min<int64_t>(grid, (n + block - 1) / block);
     a.base = 0;
     a.n = n;
-    a.n_static = std::min<int64_t>(n, grid * lblock);
+    a.n_static = std::min<int64_t>(n, grid * block);
     const bool tail = ops->project_tail != nullptr;
     const bool ctail = verdict && opts->check_collision && ops->check_tail != nullptr;
     if (tail || ctail) {
@@ -1250,8 +1280,7 @@ static mc_status project_impl(const mc_problem* p, int64_t n, const void* q_in, 
     hipLaunchKernelGGL(k_reset_u32, dim3(1), dim3(64), 0, s, counter, 4);
     if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "project_batch: reset");
     if (p->timing && (e = hipEventRecord(p->tev[0], s)) != hipSuccess) return hip_fail(e, "project_batch: timing event");
-    if (wide) e = ops->project_persistent_wide(a, int(grid), s);
-    else e = (cyc ? ops->project_persistent_cyclic : ops->project_persistent)(a, int(grid), block, s);
+    e = (cyc ? ops->project_persistent_cyclic : ops->project_persistent)(a, int(grid), block, s);
     if (e != hipSuccess) return hip_fail(e, "project_batch: persistent launch");
     if (p->timing) {
       if ((e = hipEventRecord(p->tev[1], s)) != hipSuccess) return hip_fail(e, "project_batch: timing event");

@@ -16,6 +16,7 @@
 namespace mc {
 
 constexpr int MAXJ = 36;    // joints (= DoF of kinematic families)
+constexpr int MAXW = 46;    // joint slots of the leaf-to-root walk (groups of two)
 constexpr int MAXF = 8;     // end-effector frames
 constexpr int MAXB = 6;     // constraint blocks
 constexpr int MAXM = 22;    // stacked rows
@@ -48,6 +49,10 @@ struct TP {
   T mass[MAXJ];        // link masses
   T mcom[MAXJ][3];     // mass * local centre of mass
   T submass[MAXJ];     // mass of the subtree rooted at joint j
+  // joint constants of the leaf-to-root walk in walk order, packed for wide scalar loads: origin translation o, then
+  // hc = mcom plus, for every child c of the link, submass[c] o_c, then the subtree mass (topologies with CoM
+  // rows, stride 8), or o, then the origin rotation (topologies with rotated origins, stride 16)
+  alignas(64) T jc[MAXW * 16];
   T inv_total_mass;
   T A[LIN_M][LIN_D];   // linear family (zero padded)
   T b[LIN_M];
@@ -57,7 +62,7 @@ struct TP {
 };
 
 // Kinematic and constraint constants (read by the kernels with scalar loads).
-struct alignas(16) Consts {
+struct alignas(64) Consts {
   TP<double> d;
   TP<float> f;
   int32_t dof, rows, lin_m, hull_nv;
@@ -170,12 +175,29 @@ __device__ __forceinline__ const T& after_const(const T& r, U dep) {
   asm volatile("" : "+s"(c) : "v"(dep));
   return *(const T*)c;
 }
+// The same without an order: reads that are not merged with, or hoisted to, earlier ones.
+template <class T>
+__device__ __forceinline__ const T& fresh_const(const T& r) {
+  using CT = const __attribute__((address_space(4))) T;
+  CT* c = (CT*)uniform_ptr(&r);
+  asm volatile("" : "+s"(c));
+  return *(const T*)c;
+}
 // The problem's constants as scalar-load memory.
 __device__ __forceinline__ const Consts& consts_of(const DevProblem* P) {
   using CT = const __attribute__((address_space(4))) Consts;
   CT* c = (CT*)uniform_ptr(&P->c);
   asm volatile("" : "+s"(c));
   return *(const Consts*)c;
+}
+// The kernel's argument struct (its first parameter), read again with scalar loads where it is used: kept across a
+// long loop, its fields cost scalar registers that are then spilled to vector lanes.
+template <class A>
+__device__ __forceinline__ const A& kernarg() {
+  using CT = const __attribute__((address_space(4))) A;
+  CT* c = (CT*)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(c));
+  return *(const A*)c;
 }
 // The collision data and obstacle array as scalar-load memory (wave-uniform reads).
 __device__ __forceinline__ const CollConsts& coll_of(const DevProblem* P) {
@@ -266,11 +288,19 @@ struct QLds {
   using LP = __attribute__((address_space(3))) double*;
   LP base;
   __device__ __forceinline__ double at(int j) const { return opaque(base[j * 64]); }
+  // (the opaque address is enough to keep the reads of separate passes apart, and a read that is not itself
+  // opaque is waited for at its first use)
   template <class U>
   __device__ __forceinline__ double at(int j, U dep) const {
     LP b = base;
     asm volatile("" : "+v"(b) : "v"(dep));
-    return opaque(b[j * 64]);
+    return b[j * 64];
+  }
+  __device__ __forceinline__ double get(int j) const { return base[j * 64]; }  // may be merged with another read
+  __device__ __forceinline__ QLds fresh() const {
+    QLds r = *this;
+    asm volatile("" : "+v"(r.base));
+    return r;
   }
   __device__ __forceinline__ void set(int j, double v) const { base[j * 64] = v; }
   __device__ __forceinline__ double operator[](int j) const { return at(j); }
@@ -382,5 +412,55 @@ __device__ __forceinline__ void so3_log_jlinv(const double* R, double* w, double
     Jinv[8] = a0 + beta * w[2] * w[2];
   }
 }
+
+// ---------------------------------------------------------------- step passes of a model
+// No stored sines and cosines: the model's own walks compute them from the iterate.
+struct TrigNone {
+  static constexpr bool tile = false;
+};
+
+// The passes of a projection step as the kernels call them. Direct takes them from the model itself
+// (residual rows as the scene states them); the tree models that have a leaf-to-root walk specialise
+// StepOf with it.
+template <class Model>
+struct Direct {
+  static constexpr bool trig = false;
+  template <class S>
+  using SD = typename Model::template SD<S>;
+  template <class S, uint32_t RM = ~uint32_t(0), class Q, class TR>
+  static __device__ __forceinline__ double residual(const Q& q, const Consts& C, S* F, SD<S>& sd, const TR&) {
+    return Model::template residual<S, RM>(q, C, F, sd);
+  }
+  template <class S, class Q, class TR>
+  static __device__ __forceinline__ void step_data(const Q& q, const Consts& C, SD<S>& sd, const TR&) {
+    S F[Model::M];
+    Model::template residual<S>(q, C, F, sd);
+  }
+  template <class S, uint32_t RM = ~uint32_t(0), class Q, class TR>
+  static __device__ __forceinline__ void gram(const Q& q, const Consts& C, const SD<S>& sd, const TR&, S* G) {
+    Model::template gram<S, false, RM>(q, C, sd, G, (const S*)nullptr, (S*)nullptr);
+  }
+  // G and v = J g (v in its own walk: accumulated inside the Gram walk, g and v spill)
+  template <class S, class Q, class TR, class GV>
+  static __device__ __forceinline__ void gram_jv(const Q& q, const Consts& C, const SD<S>& sd, const TR&, S* G, GV g, S* v) {
+    Model::template gram<S, false>(q, C, sd, G, g, v);
+    Model::template jv<S>(q, C, sd, g, v);
+  }
+  template <class S, uint32_t RM = ~uint32_t(0), class TR>
+  static __device__ __forceinline__ void add_lambda(S* G, const S*, S lambda, const TR&) {
+    sfor<0, Model::M>([&](auto I) {
+      constexpr int i = decltype(I)::value;
+      if constexpr ((RM >> i) & 1u) G[pidx(i, i)] += lambda;
+    });
+  }
+  template <class S, uint32_t RM = ~uint32_t(0), class Q, class TR, class OUT>
+  static __device__ __forceinline__ void jty(const Q& q, const Consts& C, const SD<S>& sd, const TR&, const S* y, OUT&& out) {
+    Model::template jty<S, RM>(q, C, sd, y, out);
+  }
+};
+template <class Model>
+struct StepOf {
+  using type = Direct<Model>;
+};
 
 }  // namespace mc

@@ -9,20 +9,22 @@
 //      the Jacobian columns need;
 //   2. convergence test ||F||^2 < tol^2 (per lane; a wave leaves the loop when every
 //      lane is done);
-//   3. Gram pass in the step precision: forward kinematics again, each Jacobian column
+//   3. Gram pass in the step precision: the tree is walked again, each Jacobian column
 //      is formed and folded into J J^T (structural nonzeros only); J is never stored;
 //   4. in-register Cholesky of J J^T (+ lambda I) with the condition estimate
 //      (max L_ii / min L_ii)^2 and forward/back substitution for y = (J J^T)^-1 F;
 //      lanes whose estimate exceeds the threshold, or whose factorisation fails,
 //      redo 1, 3 and 4 in FP64;
-//   5. J^T y pass (forward kinematics a third time), dq = alpha J^T y, optional
+//   5. J^T y pass (a third walk), dq = alpha J^T y, optional
 //      divergence exit, q <- q - dq.
+// Passes 1, 3 and 5 are those of StepOf<Model>: the model's own, or the leaf-to-root walks.
 // The persistent variant refills a lane from a device work queue as soon as its
 // configuration finishes, so lanes do not idle until the slowest configuration of
 // their wave converges.
 #pragma once
 
 #include "common.hpp"
+#include "trig.hpp"
 
 namespace mc {
 
@@ -78,6 +80,7 @@ struct QGlob {  // configuration i of a [D][ld] array in global memory
   __device__ __forceinline__ double at(int j) const { return j < dof ? double(p[j * ld + i]) : 0.0; }
   template <class U>
   __device__ __forceinline__ double at(int j, U) const { return at(j); }
+  __device__ __forceinline__ double get(int j) const { return at(j); }
 };
 
 // ------------------------------------------------------------------ Cholesky
@@ -163,28 +166,29 @@ constexpr float kFloorF32 = 0.0f;
 constexpr double kFloorF64 = 1e-24;  // pivot floor relative to the largest Gram diagonal entry
 
 // One descent step in precision S: dq = J^T (J J^T + lambda I)^-1 rhs (rhs = F for Newton;
-// overwritten). Returns false when the factorisation fails or its condition estimate
-// exceeds cond_thr.
+// overwritten). Returns false when the factorisation fails or, in FP32, its condition estimate
+// exceeds the call's threshold.
 // RM restricts the system to the rows of one block (cyclic mode).
-template <class Model, class S, uint32_t RM = ~uint32_t(0), class Q>
-__device__ __forceinline__ bool descent_step(const Q& q, S* rhs, const typename Model::template SD<S>& sd,
-                                             const Consts& C, double lambda, double cond_thr, S floor_rel, S* dq) {
+template <class Model, class S, uint32_t RM = ~uint32_t(0), class Q, class TR, class SDT>
+__device__ __forceinline__ bool descent_step(const Q& q, S* rhs, const SDT& sd, const TR& tr, const Consts& C, S floor_rel,
+                                             S* dq) {
   constexpr int M = Model::M;
+  using W = typename StepOf<Model>::type;
   S G[M * (M + 1) / 2];
-  Model::template gram<S, false, RM>(q, C, sd, G, nullptr, nullptr);
+  W::template gram<S, RM>(q, C, sd, tr, G);
+  const ProjArgs& a = kernarg<ProjArgs>();
+  if (a.lambda > 0.0) W::template add_lambda<S, RM>(G, rhs, S(a.lambda), tr);
   S maxd = S(0);
   sfor<0, M>([&](auto I) {
     constexpr int i = decltype(I)::value;
-    if constexpr ((RM >> i) & 1u) {
-      G[pidx(i, i)] += S(lambda);
-      maxd = G[pidx(i, i)] > maxd ? G[pidx(i, i)] : maxd;
-    }
+    if constexpr ((RM >> i) & 1u) maxd = G[pidx(i, i)] > maxd ? G[pidx(i, i)] : maxd;
   });
   S invd[M], kappa;
   if (!cholesky<Model, S, RM>(G, invd, kappa, floor_rel * maxd, drop_bits<Model>(sd))) return false;
-  if (!(double(kappa) <= cond_thr)) return false;
+  if constexpr (std::is_same<S, float>::value)
+    if (!(double(kappa) <= kernarg<ProjArgs>().cond_thr)) return false;
   chol_solve<Model, S, RM>(G, invd, rhs);
-  Model::template jty<S, RM>(q, C, sd, rhs, dq);
+  W::template jty<S, RM>(q, C, sd, tr, rhs, dq);
   return true;
 }
 
@@ -270,28 +274,21 @@ __device__ __forceinline__ bool descent_step_outer(const Q& q, const S* rhs, con
   return true;
 }
 
-// The step in the form the call asked for.
-template <class Model, class S, class Q>
-__device__ __forceinline__ bool step_of(const Q& q, S* rhs, const typename Model::template SD<S>& sd, const Consts& C,
-                                        const ProjArgs& a, double cond_thr, S floor_rel, S* dq) {
-  if constexpr (Model::D <= kOuterMaxD) {
-    if (a.outer) return descent_step_outer<Model, S>(q, rhs, sd, C, a.lambda, cond_thr, floor_rel, dq);
-  }
-  return descent_step<Model, S>(q, rhs, sd, C, a.lambda, cond_thr, floor_rel, dq);
-}
-
 // Apply dq (scaled by alpha) with the divergence test. Returns -1 after the update or a status.
 template <class Model, class S>
-__device__ __forceinline__ int apply_step(const QLds& q, const S* dq, const ProjArgs& a) {
+__device__ __forceinline__ int apply_step(const QLds& q, const S* dq) {
   constexpr int D = Model::D;
-  double s2 = 0.0;
+  const ProjArgs& a = kernarg<ProjArgs>();
+  const QLds qf = q.fresh();
+  double x[D], s2 = 0.0;
   for (int j = 0; j < D; ++j) {
+    x[j] = qf.get(j);
     const double d = a.alpha * double(dq[j]);
     s2 += d * d;
   }
   if (!finite_t(s2)) return ST_NONFINITE;
   if (a.max_step > 0.0 && s2 > a.max_step * a.max_step) return ST_DIVERGED;
-  for (int j = 0; j < D; ++j) q.set(j, q.at(j) - a.alpha * double(dq[j]));
+  for (int j = 0; j < D; ++j) q.set(j, x[j] - a.alpha * double(dq[j]));
   return -1;
 }
 
@@ -299,26 +296,27 @@ __device__ __forceinline__ int apply_step(const QLds& q, const S* dq, const Proj
 // precision S. Returns -1 after taking a step, else the final status; in FP32 mode ST_DEFER
 // when the FP32 factorisation fails or its condition estimate exceeds the threshold (the
 // iteration is then redone with an FP64 step, and the configuration stays in FP64 until it
-// ends).
-template <class Model, class S>
-__device__ __forceinline__ int newton_iteration(const QLds& q, int& k, const ProjArgs& a, const Consts& C, double& resid) {
+// ends). OUTER: the outer form of the step, on the model's own rows.
+template <class Model, class S, bool OUTER, class TR>
+__device__ __forceinline__ int newton_iteration(const QLds& q, const TR& tr, int& k, const Consts& C, double& resid) {
   constexpr int D = Model::D, M = Model::M;
-  typename Model::template SD<S> sd;
+  using W = std::conditional_t<OUTER, Direct<Model>, typename StepOf<Model>::type>;
+  constexpr bool f32 = std::is_same<S, float>::value;
+  typename W::template SD<S> sd;
   S F[M];
-  const double n2 = Model::template residual<S>(q, C, F, sd);
+  const double n2 = W::template residual<S>(q, C, F, sd, tr);
+  const ProjArgs& a = kernarg<ProjArgs>();
   resid = sqrt(n2);
   if (!finite_t(n2)) return ST_NONFINITE;
   if (n2 < a.tol2) return ST_CONVERGED;
   if (k >= a.max_iter) return ST_MAX_ITER;
   S dq[D];
-  int st;
-  if constexpr (std::is_same<S, float>::value) {
-    if (!step_of<Model, float>(q, F, sd, C, a, a.cond_thr, kFloorF32, dq)) return ST_DEFER;
-    st = apply_step<Model, float>(q, dq, a);
-  } else {
-    if (!step_of<Model, double>(q, F, sd, C, a, 1e300, kFloorF64, dq)) return ST_SINGULAR;
-    st = apply_step<Model, double>(q, dq, a);
-  }
+  const S floor_rel = f32 ? S(kFloorF32) : S(kFloorF64);
+  bool ok;
+  if constexpr (OUTER) ok = descent_step_outer<Model, S>(q, F, sd, C, a.lambda, f32 ? a.cond_thr : 1e300, floor_rel, dq);
+  else ok = descent_step<Model, S>(q, F, sd, tr, C, floor_rel, dq);
+  if (!ok) return f32 ? ST_DEFER : ST_SINGULAR;
+  const int st = apply_step<Model, S>(q, dq);
   if (st < 0) ++k;
   return st;
 }
@@ -329,14 +327,16 @@ __device__ __forceinline__ int newton_iteration(const QLds& q, int& k, const Pro
 // (MaxDistance) applies to the displacement of the whole iteration. q0 receives the iterate at
 // the start of the iteration. In FP32 mode a failed factorisation in any block restores that
 // iterate and returns ST_DEFER (the iteration is redone in FP64).
-template <class Model, class S>
-__device__ __forceinline__ int cyclic_iteration(const QLds& q, const QLds& q0, int& k, const ProjArgs& a,
-                                                const Consts& C, double& resid) {
+template <class Model, class S, class TR>
+__device__ __forceinline__ int cyclic_iteration(const QLds& q, const QLds& q0, const TR& tr, int& k, const Consts& C,
+                                                double& resid) {
   constexpr int D = Model::D, M = Model::M, NB = Model::NBLK;
   constexpr bool f32 = std::is_same<S, float>::value;
-  typename Model::template SD<S> sd;
+  using W = typename StepOf<Model>::type;
+  typename W::template SD<S> sd;
   S F[M];
-  const double n2 = Model::template residual<S>(q, C, F, sd);
+  const double n2 = W::template residual<S>(q, C, F, sd, tr);
+  const ProjArgs& a = kernarg<ProjArgs>();
   resid = sqrt(n2);
   if (!finite_t(n2)) return ST_NONFINITE;
   if (n2 < a.tol2) return ST_CONVERGED;
@@ -349,10 +349,9 @@ __device__ __forceinline__ int cyclic_iteration(const QLds& q, const QLds& q0, i
     constexpr uint32_t RM = Model::block_rows_mask(b);
     if (st < 0 && !failed) {
       // the first block steps from the iterate whose residual is already in F and sd
-      if constexpr (b > 0) Model::template residual<S, RM>(q, C, F, sd);
+      if constexpr (b > 0) W::template residual<S, RM>(q, C, F, sd, tr);
       S dq[D];
-      if (!descent_step<Model, S, RM>(q, F, sd, C, a.lambda, f32 ? a.cond_thr : 1e300, f32 ? S(kFloorF32) : S(kFloorF64),
-                                      dq)) {
+      if (!descent_step<Model, S, RM>(q, F, sd, tr, C, f32 ? S(kFloorF32) : S(kFloorF64), dq)) {
         failed = true;
       } else {
         double s2 = 0.0;
@@ -390,23 +389,54 @@ __device__ __forceinline__ int cyclic_iteration(const QLds& q, const QLds& q0, i
   return -1;
 }
 
-// One iteration of either mode.
-template <class Model, class S, bool CYC>
-__device__ __forceinline__ int iteration(const QLds& q, const QLds& q0, int& k, const ProjArgs& a, const Consts& C,
-                                         double& resid) {
-  if constexpr (CYC) return cyclic_iteration<Model, S>(q, q0, k, a, C, resid);
-  else return newton_iteration<Model, S>(q, k, a, C, resid);
+// The step a kernel is built for.
+enum : int { STACKED = 0, CYCLIC = 1, OUTER = 2 };
+
+// One iteration of a build.
+template <class Model, class S, int MODE, class TR>
+__device__ __forceinline__ int iteration(const QLds& q, const QLds& q0, const TR& tr, int& k, const Consts& C, double& resid) {
+  if constexpr (MODE == CYCLIC) return cyclic_iteration<Model, S>(q, q0, tr, k, C, resid);
+  else return newton_iteration<Model, S, MODE == OUTER>(q, tr, k, C, resid);
 }
 
 // Run one configuration to the end with FP64 steps.
-template <class Model, bool CYC = false>
-__device__ __forceinline__ int finish_fp64(const QLds& q, const QLds& q0, int& k, const ProjArgs& a, const Consts& C,
-                                          double& resid) {
+template <class Model, int MODE, class TR>
+__device__ __forceinline__ int finish_fp64(const QLds& q, const QLds& q0, const TR& tr, int& k, const Consts& C, double& resid) {
   int st;
   do {
-    st = iteration<Model, double, CYC>(q, q0, k, a, C, resid);
+    st = iteration<Model, double, MODE>(q, q0, tr, k, C, resid);
   } while (st < 0);
   return st;
+}
+
+// LDS of the projection and VJP kernels, in doubles: the sine table of the models that use one, the
+// per-wave [D][64] iterate tiles, what else the kernel keeps per lane, and last the tiles of sines and
+// cosines (TILE; two floats per entry).
+template <class Model>
+constexpr int kTabDoubles = StepOf<Model>::type::trig ? kSinTabDoubles : 0;
+template <class Model, bool TILE>
+using TrigFor = std::conditional_t<!StepOf<Model>::type::trig, TrigNone, std::conditional_t<TILE, TrigTile, TrigLive>>;
+// The lane's trig source; tile: the kernel's first double of trig tiles. The table is staged by the whole
+// block, before any lane leaves.
+template <class Model, bool TILE>
+__device__ __forceinline__ TrigFor<Model, TILE> make_trig(double* smem, double* tile) {
+  TrigFor<Model, TILE> t;
+  if constexpr (StepOf<Model>::type::trig) {
+    stage_sin_tab(smem);
+    __syncthreads();
+    t.tab = (SinTabP)smem;
+    if constexpr (TILE)
+      t.base = (TrigTile::LP)(reinterpret_cast<TrigTile::V2*>(tile) + (int(threadIdx.x) >> 6) * (Model::D * 64) + (int(threadIdx.x) & 63));
+  }
+  return t;
+}
+// FP32 projections of the models with trig tiles keep one (the cyclic build has no LDS left for it).
+template <class Model, class S, int MODE>
+constexpr bool kTrigTile = StepOf<Model>::type::trig && std::is_same<S, float>::value && MODE == STACKED;
+// Dynamic LDS of a projection kernel, in bytes.
+template <class Model, int MODE, bool TILE>
+constexpr size_t projection_lds(int block) {
+  return 8 * (size_t(kTabDoubles<Model>) + size_t(Model::D) * size_t(block) * (1 + (MODE == CYCLIC ? 1 : 0) + (TILE ? 1 : 0)));
 }
 
 // Configuration dimension: a compile-time constant where the model fixes it (the per-coordinate
@@ -423,10 +453,13 @@ template <class Model, class IO>
 __device__ __forceinline__ void load_q(const ProjArgs& a, int dof, int64_t i, const QLds& q) {
   const IO* p = static_cast<const IO*>(a.q_in) + a.base + i;
   const int64_t ld = a.ld_in;
+  IO x[Model::D];  // every coordinate requested before the first is waited for
   for (int c = 0; c < Model::D; ++c) {
-    q.set(c, c < dof ? double(*p) : 0.0);
+    x[c] = c < dof ? *p : IO(0);
     p += after(ld, c);
   }
+  __builtin_amdgcn_sched_barrier(0);
+  for (int c = 0; c < Model::D; ++c) q.set(c, double(x[c]));
 }
 
 template <class Model, class IO>
@@ -434,26 +467,32 @@ __device__ __forceinline__ void store_result(const ProjArgs& a, int dof, int64_t
                                              double resid) {
   IO* p = static_cast<IO*>(a.q_out) + a.base + i;
   const int64_t ld = a.ld_out;
-  for (int c = 0; c < Model::D; ++c) {
-    if (c < dof) *p = IO(q.at(c));
-    p += after(ld, c);
+  const QLds qf = q.fresh();
+  for (int c0 = 0; c0 < Model::D; c0 += 12) {  // twelve coordinates at a time
+    double x[12];
+    for (int c = 0; c < 12; ++c) x[c] = c0 + c < Model::D ? qf.get(c0 + c) : 0.0;
+    __builtin_amdgcn_sched_barrier(0);
+    for (int c = 0; c < 12; ++c) {
+      if (c0 + c < dof && c0 + c < Model::D) *p = IO(x[c]);
+      p += after(ld, c);
+    }
   }
   a.status[a.base + i] = int8_t(st);
   a.iters[a.base + i] = int8_t(k);
   st_io<IO>(a.resid, a.base + i, resid);
 }
 
-// Persistent projection kernel: a grid of resident waves pulls configurations from a device
-// work queue (atomic counter), one per lane, and refills a lane when its configuration ends.
-// Dynamic LDS: D * blockDim doubles.
 // Append the calling lane's FP64 configuration to a queue (slot < defer_cap: the queues are
 // sized for the batch).
 template <class Model, class Q>
 __device__ __forceinline__ unsigned queue_q(const Q& q, unsigned* count, double* qbuf, int64_t cap) {
   const unsigned slot = atomicAdd(count, 1u);
   double* dst = qbuf + slot;
+  double x[Model::D];
+  for (int c = 0; c < Model::D; ++c) x[c] = q.get(c);
+  __builtin_amdgcn_sched_barrier(0);
   for (int c = 0; c < Model::D; ++c) {
-    *dst = q.at(c);
+    *dst = x[c];
     dst += after(cap, c);
   }
   return slot;
@@ -462,10 +501,13 @@ __device__ __forceinline__ unsigned queue_q(const Q& q, unsigned* count, double*
 template <class Model, class IO, class Q>
 __device__ __forceinline__ void load_queued(const double* qbuf, int64_t cap, int64_t slot, const Q& q) {
   const double* src = qbuf + slot;
+  double x[Model::D];
   for (int c = 0; c < Model::D; ++c) {
-    q.set(c, *src);
+    x[c] = *src;
     src += after(cap, c);
   }
+  __builtin_amdgcn_sched_barrier(0);
+  for (int c = 0; c < Model::D; ++c) q.set(c, x[c]);
 }
 
 // Collision verdict of a configuration that ended with status st (exact check in-line).
@@ -482,27 +524,32 @@ __device__ __forceinline__ uint8_t verdict_inline(const QLds& q, const Consts& C
 // configuration's link bounds once more in FP32 and test them against the box around the
 // obstacles, so a configuration with no link near the obstacles is FREE at once, and the others
 // are queued for the exact check (k_check_tail).
-// Dynamic LDS: D * blockDim doubles.
-template <class Model, class IO, class S, bool CYC>
-__device__ __forceinline__ void persistent_body(const ProjArgs& a, double* smem) {
-  const Consts& C = consts_of(a.P);
+// Dynamic LDS: projection_lds.
+template <class Model, class IO, class S, int MODE, bool TILE>
+__device__ __forceinline__ void persistent_body(double* smem) {
+  const ProjArgs& a0 = kernarg<ProjArgs>();
+  const Consts& C = consts_of(a0.P);
   const int dof = dof_of<Model>(C);
-  const QLds q = q_lds<Model::D>(smem);
-  const QLds q0 = q_lds<Model::D>(smem + (CYC ? Model::D * blockDim.x : 0));  // cyclic: iterate at iteration start
+  double* tiles = smem + kTabDoubles<Model>;
+  const QLds q = q_lds<Model::D>(tiles);
+  const QLds q0 = q_lds<Model::D>(tiles + (MODE == CYCLIC ? Model::D * blockDim.x : 0));  // cyclic: iterate at iteration start
+  const auto tr = make_trig<Model, TILE>(smem, tiles + Model::D * blockDim.x);
   int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (i >= a.n_static) i = a.n;  // not part of the static share
+  const int64_t n = a0.n;
+  if (i >= a0.n_static) i = n;  // not part of the static share
   int k = 0;
-  if (i < a.n) load_q<Model, IO>(a, dof, i, q);
+  if (i < n) load_q<Model, IO>(a0, dof, i, q);
   constexpr bool fused = Model::broad_in_residual;
   // A converged lane that needs the broad phase waits (pending) until no lane of the wave is
   // still iterating or half the wave is waiting, so one FP32 walk serves all of them instead of
   // one walk per iteration count.
   bool pending = false;
   for (;;) {
-    const bool active = i < a.n && !pending;
+    const bool active = i < n && !pending;
     const bool any_active = __any(active);
     if (!any_active && !__any(pending)) break;
     if (fused && (!any_active || __builtin_popcountll(uint64_t(__ballot(pending))) >= 32)) {
+      const ProjArgs& a = kernarg<ProjArgs>();
       if (pending) {
         // broad phase on the converged configurations (an FP32 walk of the link bounds)
         a.verdict[i] = V_FREE;  // k_check_tail overwrites it with V_HIT if some part finds a hit
@@ -510,13 +557,14 @@ __device__ __forceinline__ void persistent_body(const ProjArgs& a, double* smem)
         pending = false;
         i = a.n_static + int64_t(atomicAdd(a.counter, 1u));
         k = 0;
-        if (i < a.n) load_q<Model, IO>(a, dof, i, q);
+        if (i < n) load_q<Model, IO>(a, dof, i, q);
       }
       continue;
     }
     if (active) {
       double resid;
-      int st = iteration<Model, S, CYC>(q, q0, k, a, C, resid);
+      int st = iteration<Model, S, MODE>(q, q0, tr, k, C, resid);
+      const ProjArgs& a = kernarg<ProjArgs>();
       if (st == ST_DEFER) {
         const unsigned slot = queue_q<Model>(q, a.defer_count, a.defer_q, a.defer_cap);
         atomicAdd(a.P->fallback_counter, 1ull);
@@ -536,30 +584,21 @@ __device__ __forceinline__ void persistent_body(const ProjArgs& a, double* smem)
       if ((st >= 0 || st == ST_DEFER) && !pending) {
         i = a.n_static + int64_t(atomicAdd(a.counter, 1u));
         k = 0;
-        if (i < a.n) load_q<Model, IO>(a, dof, i, q);
+        if (i < n) load_q<Model, IO>(a, dof, i, q);
       }
     }
   }
 }
 
 
-template <class Model, class S, bool CYC>
-constexpr int persist_waves_v = std::is_same<S, float>::value && !CYC ? PersistWaves<Model>::value : 1;
+template <class Model, class S, int MODE>
+constexpr int persist_waves_v = std::is_same<S, float>::value && MODE == STACKED ? PersistWaves<Model>::value : 1;
 
-template <class Model, class IO, class S, bool CYC = false>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(persist_waves_v<Model, S, CYC>)))
-k_project_persistent(ProjArgs a) {
+template <class Model, class IO, class S, int MODE>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(persist_waves_v<Model, S, MODE>)))
+k_project_persistent(ProjArgs) {
   extern __shared__ double smem[];
-  persistent_body<Model, IO, S, CYC>(a, smem);
-}
-
-// The same kernel compiled for two resident waves per SIMD (registers capped at 256 per lane, the
-// rest spilled): for batches larger than the lanes one wave per SIMD offers, where a second
-// round of the work queue would otherwise run with nothing to hide its latency.
-template <class Model, class IO, class S>
-__global__ void __launch_bounds__(256, 2) k_project_persistent_wide(ProjArgs a) {
-  extern __shared__ double smem[];
-  persistent_body<Model, IO, S, false>(a, smem);
+  persistent_body<Model, IO, S, MODE, kTrigTile<Model, S, MODE>>(smem);
 }
 
 // Exact collision check of the configurations queued by k_project_persistent, L lanes per
@@ -630,22 +669,25 @@ __global__ void __launch_bounds__(256) k_check_tail(ProjArgs a, int64_t small, i
 // lane (grid-stride over the queue), continued from their stored FP64 iterate with FP64 steps. Their
 // collision check joins the persistent kernel's: broad phase here, flagged ones queued for
 // k_check_tail (a one-lane exact check in-line cost C1's tail half a millisecond).
-// Dynamic LDS: D * blockDim doubles.
-template <class Model, class IO, bool CYC = false>
+// Dynamic LDS: projection_lds.
+template <class Model, class IO, int MODE>
 __global__ void __launch_bounds__(64) k_project_tail(ProjArgs a) {
   extern __shared__ double smem[];
+  const int64_t cnt = *a.defer_count;
+  if (int64_t(blockIdx.x) * blockDim.x >= cnt) return;  // no deferred work for this block
   const Consts& C = consts_of(a.P);
   const int dof = dof_of<Model>(C);
-  const QLds q = q_lds<Model::D>(smem);
-  const QLds q0 = q_lds<Model::D>(smem + (CYC ? Model::D * blockDim.x : 0));
-  const int64_t cnt = *a.defer_count;
+  double* tiles = smem + kTabDoubles<Model>;
+  const QLds q = q_lds<Model::D>(tiles);
+  const QLds q0 = q_lds<Model::D>(tiles + (MODE == CYCLIC ? Model::D * blockDim.x : 0));
+  const auto tr = make_trig<Model, false>(smem, nullptr);
   for (int64_t slot = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; slot < cnt;
        slot += int64_t(gridDim.x) * blockDim.x) {
     const int64_t i = a.defer_ik[2 * slot];
     int k = a.defer_ik[2 * slot + 1];
     load_queued<Model, IO>(a.defer_q, a.defer_cap, slot, q);
     double resid;
-    const int st = finish_fp64<Model, CYC>(q, q0, k, a, C, resid);
+    const int st = finish_fp64<Model, MODE>(q, q0, tr, k, C, resid);
     store_result<Model, IO>(a, dof, i, q, st, k, resid);
     if (a.verdict) {
       if constexpr (Model::broad_in_residual) {
@@ -667,12 +709,14 @@ __global__ void __launch_bounds__(64) k_project_tail(ProjArgs a) {
 // Plain kernel: one launch per geodesic, one configuration per lane, projection and
 // collision check in the same kernel, no work queues (the FP64 steps and the exact check of
 // flagged configurations run in-line).
-template <class Model, class IO, class S>
+template <class Model, class IO, class S, int MODE>
 __global__ void __launch_bounds__(64) k_project_plain(ProjArgs a) {
   extern __shared__ double smem[];
   const Consts& C = consts_of(a.P);
   const int dof = dof_of<Model>(C);
-  const QLds q = q_lds<Model::D>(smem);
+  double* tiles = smem + kTabDoubles<Model>;
+  const QLds q = q_lds<Model::D>(tiles);
+  const auto tr = make_trig<Model, kTrigTile<Model, S, MODE>>(smem, tiles + Model::D * blockDim.x);
   const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
   if (i >= a.n) return;
   load_q<Model, IO>(a, dof, i, q);
@@ -681,11 +725,13 @@ __global__ void __launch_bounds__(64) k_project_plain(ProjArgs a) {
   constexpr bool fused = Model::broad_in_residual;
   bool near = true;
   for (;;) {
-    st = newton_iteration<Model, S>(q, k, a, C, resid);
+    st = newton_iteration<Model, S, MODE == OUTER>(q, tr, k, C, resid);
     if (st >= 0) break;
     if (st == ST_DEFER) {  // same rule as the persistent variant: FP64 steps from here on
       atomicAdd(a.P->fallback_counter, 1ull);
-      st = finish_fp64<Model>(q, q, k, a, C, resid);
+      TrigFor<Model, false> live;
+      if constexpr (StepOf<Model>::type::trig) live.tab = tr.tab;
+      st = finish_fp64<Model, MODE>(q, q, live, k, C, resid);
       near = true;
       break;
     }
@@ -806,12 +852,18 @@ template <class Model, class IO, class S>
 __device__ __forceinline__ void vjp_load(const VjpArgs& a, int dof, int64_t i, const QLds& q, const GLds<S>& g) {
   const IO* pq = static_cast<const IO*>(a.q) + i;
   const IO* pg = static_cast<const IO*>(a.g) + i;
+  IO x[Model::D], y[Model::D];
   for (int c = 0; c < Model::D; ++c) {
-    q.set(c, c < dof ? double(*pq) : 0.0);
-    g.set(c, c < dof ? S(*pg) : S(0));
+    x[c] = c < dof ? *pq : IO(0);
+    y[c] = c < dof ? *pg : IO(0);
     const int64_t ld = after(a.ld, c);
     pq += ld;
     pg += ld;
+  }
+  __builtin_amdgcn_sched_barrier(0);
+  for (int c = 0; c < Model::D; ++c) {
+    q.set(c, double(x[c]));
+    g.set(c, S(y[c]));
   }
 }
 
@@ -823,20 +875,20 @@ __device__ __forceinline__ void vjp_fill(const VjpArgs& a, int dof, int64_t i, d
 
 // FP64 Gram, factorisation and projection for one lane: g_in = g - J^T (J J^T)^-1 J g (NaN where
 // the FP64 factorisation fails).
-template <class Model, class IO>
-__device__ __forceinline__ void vjp64(const VjpArgs& a, int dof, int64_t i, const QLds& q, const GLds<double>& g,
+template <class Model, class IO, class TR>
+__device__ __forceinline__ void vjp64(const VjpArgs& a, int dof, int64_t i, const QLds& q, const GLds<double>& g, const TR& tr,
                                       const Consts& C) {
   constexpr int M = Model::M;
-  typename Model::template SD<double> sd;
-  double F[M], G[M * (M + 1) / 2], v[M], invd[M], kappa;
-  Model::template residual<double>(q, C, F, sd);
-  Model::template gram<double, false>(q, C, sd, G, g, v);
-  Model::template jv<double>(q, C, sd, g, v);
+  using W = typename StepOf<Model>::type;
+  typename W::template SD<double> sd;
+  double G[M * (M + 1) / 2], v[M], invd[M], kappa;
+  W::template step_data<double>(q, C, sd, tr);
+  W::template gram_jv<double>(q, C, sd, tr, G, g, v);
   double maxd = 0.0;
   for (int r = 0; r < M; ++r) maxd = fmax(maxd, G[pidx(r, r)]);
   if (cholesky<Model, double>(G, invd, kappa, kFloorF64 * maxd, drop_bits<Model>(sd))) {
     chol_solve<Model, double>(G, invd, v);
-    Model::template jty<double>(q, C, sd, v, VjpOut<IO, double>{static_cast<IO*>(a.g_in) + i, a.ld, g, dof});
+    W::template jty<double>(q, C, sd, tr, v, VjpOut<IO, double>{static_cast<IO*>(a.g_in) + i, a.ld, g, dof});
   } else {
     vjp_fill<IO>(a, dof, i, __builtin_nan(""));
   }
@@ -846,14 +898,19 @@ __device__ __forceinline__ void vjp64(const VjpArgs& a, int dof, int64_t i, cons
 // pass stores nothing beyond q and status). g_in = 0 for configurations that did not converge.
 // In FP32 mode a lane whose factorisation fails or whose condition estimate exceeds the
 // threshold is queued for k_vjp_tail, which redoes it in FP64.
-// Dynamic LDS: D * blockDim doubles (iterates) + D * blockDim S (gradients).
+// Dynamic LDS: the sine table, D * blockDim doubles (iterates), D * blockDim S (gradients).
 template <class Model, class IO, class S>
 __global__ void __launch_bounds__(64) k_vjp(VjpArgs a) {
   constexpr int D = Model::D, M = Model::M;
   extern __shared__ double smem[];
+  constexpr bool f32 = std::is_same<S, float>::value;
+  using W = typename StepOf<Model>::type;
   const Consts& C = consts_of(a.P);
-  const QLds q = q_lds<D>(smem);
-  const GLds<S> g = g_lds<D, S>(smem);
+  double* tiles = smem + kTabDoubles<Model>;
+  const QLds q = q_lds<D>(tiles);
+  const GLds<S> g = g_lds<D, S>(tiles);
+  // the trig tile takes the iterate's place slot by slot: the one pass that reads the iterate writes it
+  const auto tr = make_trig<Model, W::trig && f32>(smem, tiles);
   const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
   if (i >= a.n) return;
   const int dof = dof_of<Model>(C);
@@ -862,39 +919,41 @@ __global__ void __launch_bounds__(64) k_vjp(VjpArgs a) {
     return;
   }
   vjp_load<Model, IO, S>(a, dof, i, q, g);
-  if constexpr (std::is_same<S, float>::value) {
-    typename Model::template SD<float> sd;
-    float F[M], G[M * (M + 1) / 2], v[M], invd[M], kappa;
-    Model::template residual<float>(q, C, F, sd);
-    Model::template gram<float, false>(q, C, sd, G, g, v);
-    Model::template jv<float>(q, C, sd, g, v);
+  if constexpr (f32) {
+    typename W::template SD<float> sd;
+    float G[M * (M + 1) / 2], v[M], invd[M], kappa;
+    W::template step_data<float>(q, C, sd, tr);
+    W::template gram_jv<float>(q, C, sd, tr, G, g, v);
     if (cholesky<Model, float>(G, invd, kappa, kFloorF32, drop_bits<Model>(sd)) && double(kappa) <= a.cond_thr) {
       chol_solve<Model, float>(G, invd, v);
-      Model::template jty<float>(q, C, sd, v, VjpOut<IO, float>{static_cast<IO*>(a.g_in) + i, a.ld, g, dof});
+      W::template jty<float>(q, C, sd, tr, v, VjpOut<IO, float>{static_cast<IO*>(a.g_in) + i, a.ld, g, dof});
     } else {
       atomicAdd(a.P->fallback_counter, 1ull);
       a.defer_idx[atomicAdd(a.defer_count, 1u)] = int32_t(i);
     }
   } else {
-    vjp64<Model, IO>(a, dof, i, q, g, C);
+    vjp64<Model, IO>(a, dof, i, q, g, tr, C);
   }
 }
 
 // FP64 redo of the VJPs queued by k_vjp (grid-stride over the queue).
-// Dynamic LDS: 2 * D * blockDim doubles (iterates, gradients).
+// Dynamic LDS: the sine table, 2 * D * blockDim doubles (iterates, gradients).
 template <class Model, class IO>
 __global__ void __launch_bounds__(64) k_vjp_tail(VjpArgs a) {
   constexpr int D = Model::D;
   extern __shared__ double smem[];
+  const int64_t cnt = *a.defer_count;
+  if (int64_t(blockIdx.x) * blockDim.x >= cnt) return;  // no deferred work for this block
   const Consts& C = consts_of(a.P);
   const int dof = dof_of<Model>(C);
-  const QLds q = q_lds<D>(smem);
-  const GLds<double> g = g_lds<D, double>(smem);
-  const int64_t cnt = *a.defer_count;
+  double* tiles = smem + kTabDoubles<Model>;
+  const QLds q = q_lds<D>(tiles);
+  const GLds<double> g = g_lds<D, double>(tiles);
+  const auto tr = make_trig<Model, false>(smem, nullptr);
   for (int64_t s = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; s < cnt; s += int64_t(gridDim.x) * blockDim.x) {
     const int64_t i = a.defer_idx[s];
     vjp_load<Model, IO, double>(a, dof, i, q, g);
-    vjp64<Model, IO>(a, dof, i, q, g, C);
+    vjp64<Model, IO>(a, dof, i, q, g, tr, C);
   }
 }
 

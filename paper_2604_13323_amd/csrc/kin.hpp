@@ -98,6 +98,9 @@ struct TopoDual14Rel {
   static constexpr bool has_com = false;
   static constexpr bool massless(int) { return true; }
   static constexpr bool may_have_spheres(int) { return true; }
+  // leaf-to-root order: the two arms' joints side by side
+  static constexpr int NG = 7;
+  static constexpr int walk[NG][2] = {{6, 13}, {5, 12}, {4, 11}, {3, 10}, {2, 9}, {1, 8}, {0, 7}};
 };
 
 // 6-DoF floating base (Px Py Pz Rz Ry Rx -> pelvis = link 5), legs 2 x 6, torso 2,
@@ -136,6 +139,11 @@ struct TopoHumanoid36 {
   static constexpr bool has_com = true;
   static constexpr bool massless(int j) { return j < 5; }     // the base's intermediate links
   static constexpr bool may_have_spheres(int j) { return j >= 5; }
+  // leaf-to-root order: head, both arms side by side, torso, both legs side by side, base
+  static constexpr int NG = 23;
+  static constexpr int walk[NG][2] = {{35, -1}, {34, -1}, {26, 33}, {25, 32}, {24, 31}, {23, 30}, {22, 29}, {21, 28},
+                                      {20, 27}, {19, -1}, {18, -1}, {11, 17}, {10, 16}, {9, 15}, {8, 14}, {7, 13},
+                                      {6, 12}, {5, -1}, {4, -1}, {3, -1}, {2, -1}, {1, -1}, {0, -1}};
 };
 
 // The humanoid tree with the Digit constraint set: feet poses, hands relative pose, CoM within the
@@ -175,6 +183,11 @@ struct TopoDigit36 {
   static constexpr bool has_com = true;
   static constexpr bool massless(int j) { return j < 5; }
   static constexpr bool may_have_spheres(int j) { return j >= 5; }
+  // leaf-to-root order: head, both arms side by side, torso, both legs side by side, base
+  static constexpr int NG = 23;
+  static constexpr int walk[NG][2] = {{35, -1}, {34, -1}, {26, 33}, {25, 32}, {24, 31}, {23, 30}, {22, 29}, {21, 28},
+                                      {20, 27}, {19, -1}, {18, -1}, {11, 17}, {10, 16}, {9, 15}, {8, 14}, {7, 13},
+                                      {6, 12}, {5, -1}, {4, -1}, {3, -1}, {2, -1}, {1, -1}, {0, -1}};
 };
 
 // The 7-DoF arm with one TSR pose block of finite bounds on its end-effector frame (all six
@@ -572,35 +585,40 @@ struct Kin {
   // (projection onto each segment, clamped to its ends). Inside (left of every edge): both rows
   // dropped. Nearest point inside an edge: rows [n.(x - c), 0] in the edge's frame, the second
   // dropped, row map H = [n; 0]. Nearest point a vertex v: rows x - v, H = I.
-  template <class S, int b>
-  // Each edge's constants are read after the previous edge's distance (scalar loads hoisted ahead
-  // of the kinematic walk would hold registers through it).
-  static __device__ __forceinline__ void hull_rows(double x, double y, const Consts& P0, S* F, double& n2, SD<S>& sd) {
+  // (A rolled loop, the next edge's constants in flight while one is tested: unrolled, the edges' scalar loads stood one
+  // after another.)
+  template <class S, int b, class SDT>
+  static __device__ __forceinline__ void hull_rows(double x, double y, const Consts& P0, S* F, double& n2, SDT& sd) {
     constexpr int r0 = KI::brow0(b);
-    const Consts& P = after_cp(P0, y);
+    const Consts& P = fresh_const(P0);
     const int nv = P.hull_nv;
     bool inside = true, on_edge = false;
     double best = 1e300, bx = 0.0, by = 0.0, bnx = 0.0, bny = 0.0;
-    for (int i = 0; i < MAXHV; ++i) {
-      if (i < nv) {
-        const TP<double>& Pd = after_cp(P.d, best);
-        const double* e = Pd.hull_e[i];
-        const double* nn = Pd.hull_n[i];
-        const double dx = x - e[0], dy = y - e[1];
-        inside = inside && (e[2] * dy - e[3] * dx >= 0.0);
-        const double t = (dx * e[2] + dy * e[3]) * nn[2];
-        const double tc = t < 0.0 ? 0.0 : (t > 1.0 ? 1.0 : t);
-        const double cx = e[0] + tc * e[2], cy = e[1] + tc * e[3];
-        const double d2 = (x - cx) * (x - cx) + (y - cy) * (y - cy);
-        if (d2 < best) {
-          best = d2;
-          bx = cx;
-          by = cy;
-          on_edge = t > 0.0 && t < 1.0;
-          bnx = nn[0];
-          bny = nn[1];
-        }
-      }
+    double e[4], nn[3];
+    auto edge = [&](int i, double* ee, double* en) {
+      for (int k = 0; k < 4; ++k) ee[k] = P.d.hull_e[i][k];
+      for (int k = 0; k < 3; ++k) en[k] = P.d.hull_n[i][k];
+    };
+    edge(0, e, nn);
+#pragma clang loop unroll(disable)
+    for (int i = 0; i < nv; ++i) {
+      double e1[4], n1[3];
+      edge(i + 1 < MAXHV ? i + 1 : i, e1, n1);
+      const double dx = x - e[0], dy = y - e[1];
+      inside = inside && (e[2] * dy - e[3] * dx >= 0.0);
+      const double t = (dx * e[2] + dy * e[3]) * nn[2];
+      const double tc = t < 0.0 ? 0.0 : (t > 1.0 ? 1.0 : t);
+      const double cx = e[0] + tc * e[2], cy = e[1] + tc * e[3];
+      const double d2 = (x - cx) * (x - cx) + (y - cy) * (y - cy);
+      const bool closer = d2 < best;
+      best = closer ? d2 : best;
+      bx = closer ? cx : bx;
+      by = closer ? cy : by;
+      on_edge = closer ? (t > 0.0 && t < 1.0) : on_edge;
+      bnx = closer ? nn[0] : bnx;
+      bny = closer ? nn[1] : bny;
+      for (int k = 0; k < 4; ++k) e[k] = e1[k];
+      for (int k = 0; k < 3; ++k) nn[k] = n1[k];
     }
     // branch-free: inside, both rows dropped; edge region, [n.(x - c), 0] with the second dropped;
     // vertex region, x - v
@@ -1071,3 +1089,5 @@ struct Kin {
 };
 
 }  // namespace mc
+
+#include "leaf.hpp"

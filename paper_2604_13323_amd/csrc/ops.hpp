@@ -13,10 +13,6 @@ struct FamilyOps {
   int dof_max;  // compiled D (padded for the linear family)
   hipError_t (*project_persistent)(const ProjArgs& a, int grid, int block, hipStream_t s);
   hipError_t (*project_persistent_cyclic)(const ProjArgs& a, int grid, int block, hipStream_t s);
-  // two waves per SIMD (256-thread blocks), for batches beyond the lanes of the one-wave launch;
-  // null where one wave per SIMD is not the register limit
-  hipError_t (*project_persistent_wide)(const ProjArgs& a, int grid, hipStream_t s);
-  int (*persistent_wide_blocks_per_cu)();
   hipError_t (*project_tail_cyclic)(const ProjArgs& a, int grid, hipStream_t s);  // FP32 mode only
   hipError_t (*project_plain)(const ProjArgs& a, hipStream_t s);
   hipError_t (*project_tail)(const ProjArgs& a, int grid, hipStream_t s);  // FP32 mode only
@@ -33,7 +29,7 @@ struct FamilyOps {
   hipError_t (*eval_cond)(const DevProblem* P, int64_t n, const void* q, int64_t ld, double lambda, void* kappa,
                           hipStream_t s);
   int (*persistent_blocks_per_cu)(int block);
-  size_t (*lds_bytes)(int block);
+  size_t (*lds_bytes)(int block, int cyclic);  // dynamic LDS of the persistent kernel
 };
 
 inline unsigned blocks_for(int64_t n, int block) { return unsigned((n + block - 1) / block); }
@@ -45,7 +41,12 @@ constexpr int kCheckLanes = 4;       // check_batch: lanes per configuration
 // several translation units, so their kernels compile in parallel).
 template <class Model, class IO, class S>
 struct OpsImpl {
-  static size_t lds_bytes(int block) { return size_t(Model::D) * sizeof(double) * size_t(block); }
+  static size_t tile_bytes(int block) { return size_t(Model::D) * sizeof(double) * size_t(block); }
+  static size_t lds_bytes(int block, int cyclic) {
+    return cyclic && Model::NBLK > 1 ? projection_lds<Model, CYCLIC, kTrigTile<Model, S, CYCLIC>>(block)
+                                     : projection_lds<Model, STACKED, kTrigTile<Model, S, STACKED>>(block);
+  }
+  static constexpr bool kOuter = Model::D <= kOuterMaxD;  // the outer step form has its own builds
   static hipError_t project_persistent(const ProjArgs& a, int grid, int block, hipStream_t s);
   static int persistent_blocks_per_cu(int block);
   // cyclic mode (models with several constraint blocks): a second LDS tile holds the iterate at
@@ -64,12 +65,7 @@ struct OpsImpl {
   static hipError_t eval_fj(const DevProblem* P, int64_t n, const void* q, int64_t ld, void* F, void* J, hipStream_t s);
   static hipError_t eval_cond(const DevProblem* P, int64_t n, const void* q, int64_t ld, double lambda, void* kappa,
                               hipStream_t s);
-  static hipError_t project_persistent_wide(const ProjArgs& a, int grid, hipStream_t s);
-  static int persistent_wide_blocks_per_cu();
   static constexpr bool kF32 = std::is_same<S, float>::value;
-  // the 36-DoF tree in FP32 mode needs more than 256 registers per lane: its one-wave launch
-  // leaves half the wave slots empty, which the two-wave launch fills on large batches
-  static constexpr bool kWide = Model::D > 16 && kF32;
   static FamilyOps make() {
     FamilyOps o;
     o.family = Model::family;
@@ -85,13 +81,6 @@ struct OpsImpl {
     } else {
       o.project_persistent_cyclic = &project_persistent;
       if constexpr (kF32) o.project_tail_cyclic = &project_tail;
-    }
-    if constexpr (kWide) {
-      o.project_persistent_wide = &project_persistent_wide;
-      o.persistent_wide_blocks_per_cu = &persistent_wide_blocks_per_cu;
-    } else {
-      o.project_persistent_wide = nullptr;
-      o.persistent_wide_blocks_per_cu = nullptr;
     }
     o.project_plain = &project_plain;
     o.project_tail = nullptr;

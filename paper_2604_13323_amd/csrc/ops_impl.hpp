@@ -9,35 +9,54 @@ namespace mc {
 
 template <class Model, class IO, class S>
 hipError_t OpsImpl<Model, IO, S>::project_persistent(const ProjArgs& a, int grid, int block, hipStream_t s) {
-  hipLaunchKernelGGL((k_project_persistent<Model, IO, S>), dim3(grid), dim3(block), lds_bytes(block), s, a);
+  if constexpr (kOuter) {
+    if (a.outer) {
+      hipLaunchKernelGGL((k_project_persistent<Model, IO, S, OUTER>), dim3(grid), dim3(block), lds_bytes(block, 0), s, a);
+      return hipGetLastError();
+    }
+  }
+  hipLaunchKernelGGL((k_project_persistent<Model, IO, S, STACKED>), dim3(grid), dim3(block), lds_bytes(block, 0), s, a);
   return hipGetLastError();
 }
 template <class Model, class IO, class S>
 int OpsImpl<Model, IO, S>::persistent_blocks_per_cu(int block) {
   int nb = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, reinterpret_cast<const void*>(&k_project_persistent<Model, IO, S>),
-                                                   block, lds_bytes(block)) != hipSuccess)
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, reinterpret_cast<const void*>(&k_project_persistent<Model, IO, S, STACKED>),
+                                                   block, lds_bytes(block, 0)) != hipSuccess)
     return 1;
   return nb > 0 ? nb : 1;
 }
 template <class Model, class IO, class S>
 hipError_t OpsImpl<Model, IO, S>::project_persistent_cyclic(const ProjArgs& a, int grid, int block, hipStream_t s) {
-  hipLaunchKernelGGL((k_project_persistent<Model, IO, S, true>), dim3(grid), dim3(block), 2 * lds_bytes(block), s, a);
+  hipLaunchKernelGGL((k_project_persistent<Model, IO, S, CYCLIC>), dim3(grid), dim3(block), lds_bytes(block, 1), s, a);
   return hipGetLastError();
 }
 template <class Model, class IO, class S>
 hipError_t OpsImpl<Model, IO, S>::project_tail_cyclic(const ProjArgs& a, int grid, hipStream_t s) {
-  hipLaunchKernelGGL((k_project_tail<Model, IO, true>), dim3(grid), dim3(64), 2 * lds_bytes(64), s, a);
+  hipLaunchKernelGGL((k_project_tail<Model, IO, CYCLIC>), dim3(grid), dim3(64), (projection_lds<Model, CYCLIC, false>(64)), s, a);
   return hipGetLastError();
 }
 template <class Model, class IO, class S>
 hipError_t OpsImpl<Model, IO, S>::project_plain(const ProjArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL((k_project_plain<Model, IO, S>), dim3(blocks_for(a.n, 64)), dim3(64), lds_bytes(64), s, a);
+  if constexpr (kOuter) {
+    if (a.outer) {
+      hipLaunchKernelGGL((k_project_plain<Model, IO, S, OUTER>), dim3(blocks_for(a.n, 64)), dim3(64), lds_bytes(64, 0), s, a);
+      return hipGetLastError();
+    }
+  }
+  hipLaunchKernelGGL((k_project_plain<Model, IO, S, STACKED>), dim3(blocks_for(a.n, 64)), dim3(64), lds_bytes(64, 0), s, a);
   return hipGetLastError();
 }
 template <class Model, class IO, class S>
 hipError_t OpsImpl<Model, IO, S>::project_tail(const ProjArgs& a, int grid, hipStream_t s) {
-  hipLaunchKernelGGL((k_project_tail<Model, IO>), dim3(grid), dim3(64), lds_bytes(64), s, a);
+  constexpr size_t lds = projection_lds<Model, STACKED, false>(64);
+  if constexpr (kOuter) {
+    if (a.outer) {
+      hipLaunchKernelGGL((k_project_tail<Model, IO, OUTER>), dim3(grid), dim3(64), lds, s, a);
+      return hipGetLastError();
+    }
+  }
+  hipLaunchKernelGGL((k_project_tail<Model, IO, STACKED>), dim3(grid), dim3(64), lds, s, a);
   return hipGetLastError();
 }
 template <class Model, class IO, class S>
@@ -65,7 +84,7 @@ hipError_t OpsImpl<Model, IO, S>::check_tail(const ProjArgs& a, int grid, hipStr
 }
 template <class Model, class IO, class S>
 hipError_t OpsImpl<Model, IO, S>::vjp_tail(const VjpArgs& a, int grid, hipStream_t s) {
-  hipLaunchKernelGGL((k_vjp_tail<Model, IO>), dim3(grid), dim3(64), 2 * lds_bytes(64), s, a);
+  hipLaunchKernelGGL((k_vjp_tail<Model, IO>), dim3(grid), dim3(64), 8 * size_t(kTabDoubles<Model>) + 2 * tile_bytes(64), s, a);
   return hipGetLastError();
 }
 template <class Model, class IO, class S>
@@ -91,7 +110,7 @@ hipError_t OpsImpl<Model, IO, S>::check_broad(const CheckArgs& a, unsigned* coun
 template <class Model, class IO, class S>
 hipError_t OpsImpl<Model, IO, S>::vjp(const VjpArgs& a, hipStream_t s) {
   hipLaunchKernelGGL((k_vjp<Model, IO, S>), dim3(blocks_for(a.n, 64)), dim3(64),
-                     lds_bytes(64) + size_t(Model::D) * sizeof(S) * 64, s, a);
+                     8 * size_t(kTabDoubles<Model>) + tile_bytes(64) + size_t(Model::D) * sizeof(S) * 64, s, a);
   return hipGetLastError();
 }
 template <class Model, class IO, class S>
@@ -109,24 +128,10 @@ hipError_t OpsImpl<Model, IO, S>::eval_fj(const DevProblem* P, int64_t n, const 
 template <class Model, class IO, class S>
 hipError_t OpsImpl<Model, IO, S>::eval_cond(const DevProblem* P, int64_t n, const void* q, int64_t ld, double lambda,
                                             void* kappa, hipStream_t s) {
-  hipLaunchKernelGGL((k_eval_cond<Model, IO, S>), dim3(blocks_for(n, 64)), dim3(64), lds_bytes(64), s, P, n, q, ld,
+  hipLaunchKernelGGL((k_eval_cond<Model, IO, S>), dim3(blocks_for(n, 64)), dim3(64), tile_bytes(64), s, P, n, q, ld,
                      lambda, kappa);
   return hipGetLastError();
 }
-template <class Model, class IO, class S>
-hipError_t OpsImpl<Model, IO, S>::project_persistent_wide(const ProjArgs& a, int grid, hipStream_t s) {
-  hipLaunchKernelGGL((k_project_persistent_wide<Model, IO, S>), dim3(grid), dim3(256), lds_bytes(256), s, a);
-  return hipGetLastError();
-}
-template <class Model, class IO, class S>
-int OpsImpl<Model, IO, S>::persistent_wide_blocks_per_cu() {
-  int nb = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, reinterpret_cast<const void*>(&k_project_persistent_wide<Model, IO, S>),
-                                                   256, lds_bytes(256)) != hipSuccess)
-    return 1;
-  return nb > 0 ? nb : 1;
-}
-
 }  // namespace mc
 
 // Explicit instantiation of single launchers of a launcher class O = OpsImpl<M, IO, S> (named through
@@ -138,9 +143,6 @@ int OpsImpl<Model, IO, S>::persistent_wide_blocks_per_cu() {
 #define MC_INST_PERSISTENT_CYCLIC(O) \
   template hipError_t O::project_persistent_cyclic(const mc::ProjArgs&, int, int, hipStream_t);
 #define MC_INST_TAIL_CYCLIC(O) template hipError_t O::project_tail_cyclic(const mc::ProjArgs&, int, hipStream_t);
-#define MC_INST_WIDE(O)                                                                              \
-  template hipError_t O::project_persistent_wide(const mc::ProjArgs&, int, hipStream_t);             \
-  template int O::persistent_wide_blocks_per_cu();
 #define MC_INST_PLAIN(O) template hipError_t O::project_plain(const mc::ProjArgs&, hipStream_t);
 #define MC_INST_TAIL(O) template hipError_t O::project_tail(const mc::ProjArgs&, int, hipStream_t);
 #define MC_INST_CHECK(O)                                                                             \
