@@ -404,13 +404,13 @@ __global__ void k_reset_u32(unsigned int* p, int n) {
   if (int(threadIdx.x) < n) p[threadIdx.x] = 0u;
 }
 
+template <class IO>
+__global__ void k_zero1(IO* p) { *p = IO(0); }
+
 __global__ void k_fill_u8(uint8_t* p, int64_t n, uint8_t v) {
   const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
   if (i < n) p[i] = v;
 }
-
-template <class IO>
-__global__ void k_zero1(IO* p) { *p = IO(0); }
 
 __device__ __forceinline__ int find_geo(const int32_t* offs, int n_geo, int64_t i) {
   int lo = 0, hi = n_geo;  // offs[lo] <= i < offs[hi]
@@ -419,21 +419,6 @@ __device__ __forceinline__ int find_geo(const int32_t* offs, int n_geo, int64_t 
     if (offs[mid] <= i) lo = mid; else hi = mid;
   }
   return lo;
-}
-
-template <class IO>
-__global__ void k_interpolate(int n_geo, const int32_t* offs, const IO* e, int64_t ld_e, int64_t total, IO* q,
-                              int64_t ld, int d) {
-  const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (i >= total || i >= int64_t(offs[n_geo])) return;
-  const int g = find_geo(offs, n_geo, i);
-  const int L = offs[g + 1] - offs[g];
-  if (L <= 0) return;
-  const double t = double(i - offs[g] + 1) / double(L + 1);
-  for (int c = 0; c < d; ++c) {
-    const double a = double(e[c * ld_e + 2 * g]), b = double(e[c * ld_e + 2 * g + 1]);
-    q[c * ld + i] = IO(a + t * (b - a));
-  }
 }
 
 // The geodesic holding configuration i, found by one wavefront: each round, the 64 lanes probe
@@ -458,15 +443,85 @@ __device__ __forceinline__ int half_wave_find_geo(const int32_t* offs, int n_geo
 
 // The geodesics a workgroup's configurations [i0, i1] belong to: the first wavefront finds the
 // first (lanes 0-31) and the last one (lanes 32-63) in 32-ary searches side by side, the workgroup
-// stages the offsets between them in LDS (when they fit) and searches there.
+// stages the offsets between them in LDS (when they fit), and each configuration searches there.
 constexpr int kGeoWindow = 1024;
-constexpr int kMaxD = 36;  // largest configuration dimension of the compiled families
+constexpr int kMaxD = 36;   // largest configuration dimension of the compiled families
+constexpr int kCoords = 9;  // coordinates per thread of the geodesic kernels: kMaxD over four threads
+
+struct GeoWindow {
+  int32_t offs[kGeoWindow];
+  int g[2];
+};
+// The first and last geodesic into s.g, the offsets into s.offs; returns how many (more than kGeoWindow: not staged).
+// Called by the whole workgroup.
+__device__ __forceinline__ int stage_geo(GeoWindow& s, const int32_t* offs, int n_geo, int64_t i0, int64_t i1) {
+  if (threadIdx.x < 64) {
+    const int gx = half_wave_find_geo(offs, n_geo, threadIdx.x < 32 ? i0 : i1);
+    if ((threadIdx.x & 31) == 0) s.g[threadIdx.x >> 5] = gx;
+  }
+  __syncthreads();
+  const int w = s.g[1] - s.g[0] + 2;  // offsets g0 .. g1 + 1
+  if (w <= kGeoWindow)
+    for (int t = threadIdx.x; t < w; t += blockDim.x) s.offs[t] = offs[s.g[0] + t];
+  __syncthreads();
+  return w;
+}
+// Configuration i's geodesic: its index, and its first and one-past-last configuration.
+__device__ __forceinline__ int geo_of(const GeoWindow& s, int w, const int32_t* offs, int n_geo, int64_t i, int64_t& lo_off,
+                                      int64_t& hi_off) {
+  if (w > kGeoWindow) {
+    const int g = find_geo(offs, n_geo, i);
+    lo_off = offs[g];
+    hi_off = offs[g + 1];
+    return g;
+  }
+  int lo = 0, hi = w - 1;  // s.offs[lo] <= i < s.offs[hi]
+  while (hi - lo > 1) {
+    const int mid = (lo + hi) >> 1;
+    if (s.offs[mid] <= i) lo = mid; else hi = mid;
+  }
+  lo_off = s.offs[lo];
+  hi_off = s.offs[lo + 1];
+  return s.g[0] + lo;
+}
+
+// One thread per configuration and kCoords coordinates (blockIdx.y). Bound by the latency of the offset search and
+// the endpoint reads: a binary search of the offsets in global memory by every thread (12 dependent reads for 4,096
+// geodesics) and 72 endpoint reads in turn took 16.5 us for 74,059 humanoid configurations; the staged
+// search and four times the threads take 8.4 us.
+template <class IO>
+__global__ void __launch_bounds__(256) k_interpolate(int n_geo, const int32_t* offs, const IO* e, int64_t ld_e, int64_t total,
+                                                     IO* q, int64_t ld, int d) {
+  __shared__ GeoWindow s;
+  const int64_t i0 = int64_t(blockIdx.x) * blockDim.x;
+  const int64_t i1 = (i0 + blockDim.x < total ? i0 + blockDim.x : total) - 1;
+  const int64_t i = i0 + threadIdx.x;
+  const int w = stage_geo(s, offs, n_geo, i0, i1);
+  if (i >= total || i >= int64_t(offs[n_geo])) return;
+  int64_t lo, hi;
+  const int g = geo_of(s, w, offs, n_geo, i, lo, hi);
+  const int L = int(hi - lo);
+  if (L <= 0) return;
+  const double t = double(i - lo + 1) / double(L + 1);
+  const int c0 = blockIdx.y * kCoords;
+  IO a[kCoords], b[kCoords];
+#pragma unroll
+  for (int k = 0; k < kCoords; ++k) {
+    const int c = c0 + k < d ? c0 + k : d - 1;
+    a[k] = e[c * ld_e + 2 * g];
+    b[k] = e[c * ld_e + 2 * g + 1];
+  }
+#pragma unroll
+  for (int k = 0; k < kCoords; ++k) {
+    const double x = double(a[k]), y = double(b[k]);
+    if (c0 + k < d) q[(c0 + k) * ld + i] = IO(x + t * (y - x));
+  }
+}
 
 template <class IO>
 __global__ void __launch_bounds__(256) k_path_grad(int64_t n, const IO* q, int64_t ld, const int32_t* offs, int n_geo,
                                                    IO* g, IO* loss, int d) {
-  __shared__ int32_t s_offs[kGeoWindow];
-  __shared__ int s_g[2];
+  __shared__ GeoWindow s;
   const int64_t i0 = int64_t(blockIdx.x) * blockDim.x;
   const int64_t i1 = (i0 + blockDim.x < n ? i0 + blockDim.x : n) - 1;
   const int64_t i = i0 + threadIdx.x;
@@ -475,32 +530,9 @@ __global__ void __launch_bounds__(256) k_path_grad(int64_t n, const IO* q, int64
   // geodesic search
   IO x[kMaxD];
   for (int c = 0; c < kMaxD; ++c) x[c] = (act && c < d) ? q[int64_t(c) * ld + i] : IO(0);
-  if (threadIdx.x < 64) {
-    const int gx = half_wave_find_geo(offs, n_geo, threadIdx.x < 32 ? i0 : i1);
-    if ((threadIdx.x & 31) == 0) s_g[threadIdx.x >> 5] = gx;
-  }
-  __syncthreads();
-  const int g0 = s_g[0], w = s_g[1] - g0 + 2;  // offsets g0 .. g1 + 1
-  const bool win = w <= kGeoWindow;
-  if (win)
-    for (int t = threadIdx.x; t < w; t += blockDim.x) s_offs[t] = offs[g0 + t];
-  __syncthreads();
+  const int w = stage_geo(s, offs, n_geo, i0, i1);
   int64_t lo_off = 0, hi_off = 0;  // the configuration's geodesic is [lo_off, hi_off)
-  if (act) {
-    if (win) {
-      int lo = 0, hi = w - 1;  // s_offs[lo] <= i < s_offs[hi]
-      while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (s_offs[mid] <= i) lo = mid; else hi = mid;
-      }
-      lo_off = s_offs[lo];
-      hi_off = s_offs[lo + 1];
-    } else {
-      const int gi = find_geo(offs, n_geo, i);
-      lo_off = offs[gi];
-      hi_off = offs[gi + 1];
-    }
-  }
+  if (act) geo_of(s, w, offs, n_geo, i, lo_off, hi_off);
   // the searches clamp to the first and last geodesic: a configuration before geo_offsets[0] or
   // from geo_offsets[n_geo] on lies on none
   const bool inside = act && lo_off <= i && i < hi_off;
@@ -552,17 +584,32 @@ __global__ void __launch_bounds__(256) k_path_grad(int64_t n, const IO* q, int64
   }
 }
 
-__global__ void k_geo_ok(int n_geo, const int32_t* offs, int64_t n, const int8_t* status, const uint8_t* verdict, uint8_t* ok) {
-  const int g = blockIdx.x * blockDim.x + threadIdx.x;
-  if (g >= n_geo) return;
-  uint8_t r = 1;
+// Per-geodesic success: L lanes read a geodesic's statuses and verdicts, four each at a time. One thread per
+// geodesic, a byte at a time, took 30 us for 4,000 geodesics of 4 to 128 configurations; this takes 4.8 us.
+template <int L>
+__global__ void __launch_bounds__(256) k_geo_ok(int n_geo, const int32_t* offs, int64_t n, const int8_t* status,
+                                                const uint8_t* verdict, uint8_t* ok) {
+  const int64_t gid = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+  const int64_t g = gid / L;
+  if (g >= n_geo) return;  // whole groups leave together
+  const int t = int(gid) & (L - 1);
   const int64_t lo = offs[g] < 0 ? 0 : offs[g];
   const int64_t hi = offs[g + 1] < n ? offs[g + 1] : n;
-  for (int64_t i = lo; i < hi; ++i) {
-    if (status[i] != ST_CONVERGED) r = 0;
-    if (verdict && verdict[i] != V_FREE) r = 0;
+  bool bad = false;
+  for (int64_t i = lo + t; i < hi; i += 4 * L) {
+    int8_t st[4];
+    uint8_t vd[4];
+    for (int k = 0; k < 4; ++k) {
+      const int64_t j = i + k * L < hi ? i + k * L : i;
+      st[k] = status[j];
+      vd[k] = verdict ? verdict[j] : uint8_t(V_FREE);
+    }
+    for (int k = 0; k < 4; ++k) bad = bad || st[k] != ST_CONVERGED || vd[k] != V_FREE;
   }
-  ok[g] = r;
+  const int shift = int(__lane_id()) & ~(L - 1);
+  const uint64_t mask = L == 64 ? ~uint64_t(0) : ((uint64_t(1) << (L & 63)) - 1);
+  const uint64_t m = (uint64_t(__ballot(bad)) >> shift) & mask;
+  if (t == 0) ok[g] = m == 0 ? 1 : 0;
 }
 
 
@@ -1292,7 +1339,12 @@ static mc_status project_impl(const mc_problem* p, int64_t n, const void* q_in, 
     if (ctail && (e = ops->check_tail(a, kCheckTailBlocksPerCu * p->n_cu, s)) != hipSuccess) return hip_fail(e, "project_batch: check tail launch");
   }
   if (geo_ok) {
-    hipLaunchKernelGGL(k_geo_ok, dim3((n_geo + 255) / 256), dim3(256), 0, s, n_geo, geo_offsets, n, status, verdict, geo_ok);
+    // 16 lanes per geodesic (one round of four each up to 64 configurations), a wave where they average more: 524,288
+    // configurations in geodesics of 16 take 3.3 us with 16 lanes and 7.0 with a wave, of 1,024 they take 9.4 and 4.0
+    if (n / n_geo <= 64)
+      hipLaunchKernelGGL(k_geo_ok<16>, dim3(blocks_for(int64_t(n_geo) * 16, 256)), dim3(256), 0, s, n_geo, geo_offsets, n, status, verdict, geo_ok);
+    else
+      hipLaunchKernelGGL(k_geo_ok<64>, dim3(blocks_for(int64_t(n_geo) * 64, 256)), dim3(256), 0, s, n_geo, geo_offsets, n, status, verdict, geo_ok);
     if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "project_batch: geo_ok");
   }
   return MC_OK;
@@ -1453,7 +1505,7 @@ mc_status interpolate_geodesics(const mc_problem* p, int32_t n_geo, const int32_
   if (total > (int64_t(1) << 31) - 1) return fail(MC_ERR_INVALID_ARG, "interpolate_geodesics: total too large");
   if (ld_out < total) return fail(MC_ERR_INVALID_ARG, "interpolate_geodesics: ld_out < total");
   hipStream_t s = static_cast<hipStream_t>(stream);
-  const dim3 g(unsigned((total + 255) / 256)), b(256);
+  const dim3 g(unsigned((total + 255) / 256), unsigned((p->d + kCoords - 1) / kCoords)), b(256);
   if (dtype == MC_F64)
     hipLaunchKernelGGL(k_interpolate<double>, g, b, 0, s, n_geo, geo_offsets, static_cast<const double*>(endpoints), ld_e,
                        total, static_cast<double*>(q_out), ld_out, p->d);
