@@ -337,11 +337,10 @@ mc_status mc_queue_counts(const mc_problem* p, uint32_t counts[4]);
 
 /* mc_set_check_lanes — lanes per configuration of the exact collision check that project_batch
    (fused variant), extend_batch and check_batch run on the configurations their broad phase flags
-   (Sec. IV-B, the collision test of every projected configuration). 0 (the default): by the length of
-   the queue, a wave per configuration while it is short (at most 4 per launch workgroup), else groups
-   of 4 lanes (or the size mc_autotune_project chose); 1, 2, 4, 8, 16 or 64: that many on every queue. Groups below 4 lanes exist for families
-   of at most 16 coordinates and run only where the scene's staged spheres leave LDS room for them
-   (else 4). Verdicts do not depend on it. MC_ERR_INVALID_ARG for other values. */
+   (Sec. IV-B, the collision test of every projected configuration). 0 (the default): one
+   (or, on queues longer than 4 per launch workgroup, the group size mc_autotune_project chose); 1, 2, 4, 8, 16 or
+   64: that many on every queue. Groups of 2 lanes exist for families of at most 16 coordinates and run only
+   where the scene's staged spheres leave LDS room for them (else 4). Verdicts do not depend on it. MC_ERR_INVALID_ARG for other values. */
 mc_status mc_set_check_lanes(mc_problem* p, int32_t lanes);
 
 /* mc_set_kernel_timing — diagnostic: when on, project_batch brackets its main projection launch
@@ -375,7 +374,7 @@ int32_t mc_autotune_candidates(mc_launch_shape* shapes);
    naming the shape), and stores the fastest shape in the problem for opts->dtype and opts->mode.
    best (nullable) receives it, ms (nullable, float[mc_autotune_candidates()]) the mean time per
    call of every candidate. Where check_collision is on and the batch's exact-check queue is long (more
-   entries than 16 per CU), a second stage times the check's lane groups of 1, 2 (families of at most
+   entries than 16 per CU), a second stage times the check with 1, 2 (families of at most
    16 coordinates), 4, 8 and 16 lanes per configuration in the fastest shape, checks the outputs again and keeps the fastest group size in
    the problem for every later call's long queues (best->check_lanes; mc_set_check_lanes overrides it).
    The batch itself is only read. Allocates temporary outputs and synchronises the device (a set-up

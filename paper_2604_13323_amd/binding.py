@@ -376,7 +376,7 @@ class Problem:
         return out.as_dict() if rc == 0 else None
 
     def set_check_lanes(self, lanes=0):
-        """Lanes per configuration of the exact collision check (0: by queue length; 1, 2, 4, 8, 16, 64)."""
+        """Lanes per configuration of the exact collision check (0: the default choice; 1, 2, 4, 8, 16, 64)."""
         _check(lib().mc_set_check_lanes(self._h, int(lanes)), "mc_set_check_lanes")
 
     def kernel_timing(self, on=True):

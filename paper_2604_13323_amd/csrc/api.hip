@@ -261,12 +261,10 @@ bool validate_family(const HScene& s, std::string& err) {
 }
 
 // ---- obstacle clusters: recursive median split on the widest axis, <= kClusterSize each
-constexpr int kClusterSize = 16;
 constexpr double kBoundMargin = 1e-4;  // metres added to every bound (covers FP32 rounding)
 // exact-check tail grid: workgroups of 256 per CU (its short-queue path takes up to 4 waves' work
 // items per workgroup)
 constexpr int kCheckTailBlocksPerCu = 4;
-constexpr int kGroupSize = 8;          // clusters per group (the second level of boxes)
 static_assert((MAXC + kGroupSize - 1) / kGroupSize <= MAXSUP, "group table too small");
 
 void build_clusters(std::vector<std::array<double, 4>>& obs, int lo, int hi,
@@ -844,6 +842,7 @@ struct mc_problem {
   size_t max_lds_per_block = 0;
   DevProblem* dev = nullptr;
   float4* obs = nullptr;
+  float4* obs_pad = nullptr;
   int n_obs = 0, n_sph = 0;
   unsigned int* counter = nullptr;  // [0] work-queue head, [1] projection FP64 queue, [2] VJP FP64 queue,
                                     // [3] exact-check queue
@@ -862,10 +861,9 @@ struct mc_problem {
   mutable int occ[2][3] = {{0, 0, 0}, {0, 0, 0}};
   // launch shape stored by mc_autotune_project, by (FP64 mode, cyclic mode); waves_per_block 0 = none
   mc_launch_shape tuned[2][2] = {{{0, 0, 0}, {0, 0, 0}}, {{0, 0, 0}, {0, 0, 0}}};
-  // mc_set_check_lanes: lanes per configuration of the exact-check tail (0: by queue length)
+  // mc_set_check_lanes: lanes per configuration of the exact check (0: check_long, or one)
   int32_t check_lanes = 0;
-  // lanes per configuration of the exact-check tail on long queues, as mc_autotune_project chose
-  // them (0: not tuned, kTailCheckLanesLong)
+  // lanes per configuration of the exact check on long queues, as mc_autotune_project chose them (0: not tuned, one)
   int32_t check_long = 0;
   // mc_set_kernel_timing: events around the main projection launch [0, 1] and the VJP launch [2, 3]
   bool timing = false;
@@ -938,6 +936,7 @@ void mc_problem_destroy(mc_problem* p) {
     if (ev) (void)hipEventDestroy(ev);
   hipFree(p->dev);
   hipFree(p->obs);
+  hipFree(p->obs_pad);
   hipFree(p->counter);
   hipFree(p->fallback);
   hipFree(p->defer_q);
@@ -1055,6 +1054,17 @@ mc_status mc_problem_create(const void* blob, size_t nbytes, mc_problem** out) {
   K.n_clus = int(cl.size());
   std::vector<float4> obs_f(obs.size());
   for (size_t i = 0; i < obs.size(); ++i) obs_f[i] = make_float4(float(obs[i][0]), float(obs[i][1]), float(obs[i][2]), float(obs[i][3]));
+  std::vector<float4> pad_f(cl.size() * kClusterSize, make_float4(1e18f, 1e18f, 1e18f, 0.f));
+  for (size_t i = 0; i < cl.size(); ++i)
+    for (int o = rg[i][0]; o < rg[i][1]; ++o) pad_f[i * kClusterSize + size_t(o - rg[i][0])] = obs_f[o];
+  for (int i = 0; i < MAXC; ++i) {
+    K.clus_box[2 * i] = make_float4(1e30f, 1e30f, 1e30f, 0.f);
+    K.clus_box[2 * i + 1] = make_float4(-1e30f, -1e30f, -1e30f, 0.f);
+  }
+  for (int i = 0; i < MAXSUP; ++i) {
+    K.sup_box[2 * i] = make_float4(1e30f, 1e30f, 1e30f, 0.f);
+    K.sup_box[2 * i + 1] = make_float4(-1e30f, -1e30f, -1e30f, 0.f);
+  }
   // cluster boxes (bounding the obstacle spheres, inflated), then groups of up to kGroupSize
   // consecutive clusters (neighbours in the median-split order) with the union box
   std::vector<std::array<double, 6>> box(cl.size());
@@ -1067,8 +1077,11 @@ mc_status mc_problem_create(const void* blob, size_t nbytes, mc_problem** out) {
       }
     for (int a = 0; a < 3; ++a) { b[a] -= kBoundMargin; b[3 + a] += kBoundMargin; }
     box[i] = b;
-    K.clus_lo[i] = make_float4(float(b[0]), float(b[1]), float(b[2]), 0.f);
-    K.clus_hi[i] = make_float4(float(b[3]), float(b[4]), float(b[5]), 0.f);
+    const int32_t count = rg[i][1] - rg[i][0];
+    float count_bits;
+    std::memcpy(&count_bits, &count, sizeof count);
+    K.clus_box[2 * i] = make_float4(float(b[0]), float(b[1]), float(b[2]), count_bits);
+    K.clus_box[2 * i + 1] = make_float4(float(b[3]), float(b[4]), float(b[5]), 0.f);
     K.clus_range[i] = make_int2(rg[i][0], rg[i][1]);
   }
   K.n_sup = 0;
@@ -1077,8 +1090,8 @@ mc_status mc_problem_create(const void* blob, size_t nbytes, mc_problem** out) {
     std::array<double, 6> b{1e300, 1e300, 1e300, -1e300, -1e300, -1e300};
     for (size_t c = c0; c < c1; ++c)
       for (int a = 0; a < 3; ++a) { b[a] = std::min(b[a], box[c][a]); b[3 + a] = std::max(b[3 + a], box[c][3 + a]); }
-    K.sup_lo[K.n_sup] = make_float4(float(b[0]), float(b[1]), float(b[2]), 0.f);
-    K.sup_hi[K.n_sup] = make_float4(float(b[3]), float(b[4]), float(b[5]), 0.f);
+    K.sup_box[2 * (K.n_sup)] = make_float4(float(b[0]), float(b[1]), float(b[2]), 0.f);
+    K.sup_box[2 * (K.n_sup) + 1] = make_float4(float(b[3]), float(b[4]), float(b[5]), 0.f);
     K.sup_range[K.n_sup] = make_int2(int(c0), int(c1));
     ++K.n_sup;
   }
@@ -1106,6 +1119,7 @@ mc_status mc_problem_create(const void* blob, size_t nbytes, mc_problem** out) {
   auto alloc = [&](void** ptr, size_t bytes) -> hipError_t { return hipMalloc(ptr, bytes > 0 ? bytes : 16); };
   if ((e = alloc((void**)&p->dev, sizeof(DevProblem))) != hipSuccess ||
       (e = alloc((void**)&p->obs, obs_f.size() * sizeof(float4))) != hipSuccess ||
+      (e = alloc((void**)&p->obs_pad, pad_f.size() * sizeof(float4))) != hipSuccess ||
       (e = alloc((void**)&p->counter, 4 * sizeof(unsigned int))) != hipSuccess ||
       (e = alloc((void**)&p->fallback, sizeof(unsigned long long))) != hipSuccess) {
     mc_problem_destroy(p);
@@ -1113,6 +1127,7 @@ mc_status mc_problem_create(const void* blob, size_t nbytes, mc_problem** out) {
     return hip_fail(e, "mc_problem_create: hipMalloc");
   }
   hp->obs = p->obs;
+  hp->obs_pad = p->obs_pad;
   hp->fallback_counter = p->fallback;
   p->n_obs = K.n_obs;
   p->n_sph = K.n_sph;
@@ -1120,7 +1135,7 @@ mc_status mc_problem_create(const void* blob, size_t nbytes, mc_problem** out) {
   const unsigned int zero32[4] = {0, 0, 0, 0};
   if ((e = hipMemcpy(p->dev, hp, sizeof(DevProblem), hipMemcpyHostToDevice)) != hipSuccess ||
       (!obs_f.empty() && (e = hipMemcpy(p->obs, obs_f.data(), obs_f.size() * sizeof(float4), hipMemcpyHostToDevice)) != hipSuccess) ||
-
+      (!pad_f.empty() && (e = hipMemcpy(p->obs_pad, pad_f.data(), pad_f.size() * sizeof(float4), hipMemcpyHostToDevice)) != hipSuccess) ||
       (e = hipMemcpy(p->counter, zero32, sizeof zero32, hipMemcpyHostToDevice)) != hipSuccess ||
       (e = hipMemcpy(p->fallback, &zero64, sizeof zero64, hipMemcpyHostToDevice)) != hipSuccess) {
     mc_problem_destroy(p);
@@ -1870,9 +1885,9 @@ mc_status mc_autotune_project(mc_problem* p, int64_t n, const void* q_in, int64_
     }
   }
   // second stage, where the batch's exact-check queue is long (more entries than the tail's
-  // wave-per-configuration path takes): the lane groups of that queue, in the best shape (groups of 1
-  // and 2 only for the families that have them; the kernel rounds them up to 4 where the scene's
-  // staged spheres leave no LDS room for them)
+  // wave-per-configuration path takes): one lane per configuration and the lane groups, in the best shape (groups of
+  // 2 only for the families that have them; the kernel rounds them up to 4 where the scene's staged spheres leave no
+  // LDS room for them)
   mc_launch_shape chosen = kTuneCandidates[best_c >= 0 ? best_c : 0];
   unsigned queued = 0;
   if (rc == MC_OK && opts->check_collision &&
@@ -1883,7 +1898,7 @@ mc_status mc_autotune_project(mc_problem* p, int64_t n, const void* q_in, int64_
     int32_t best_l = 0;
     float best_l_ms = 0.f;
     for (int32_t L : {1, 2, 4, 8, 16}) {
-      if (L < 4 && p->d > kTailCheckLowLanesMaxD) continue;  // such families run groups of at least 4
+      if (L == 2 && p->d > kTailCheckLowLanesMaxD) continue;  // such families run no groups of 2
       mc_project_opts o = *opts;
       o.variant = 2;
       o.waves_per_block = chosen.waves_per_block;

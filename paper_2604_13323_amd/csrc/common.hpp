@@ -69,6 +69,8 @@ struct alignas(64) Consts {
 };
 
 constexpr int MAXSUP = 32;  // groups of obstacle clusters
+constexpr int kClusterSize = 16;  // obstacles in a cluster, at most
+constexpr int kGroupSize = 8;     // clusters in a group
 
 // Collision data. Obstacles are grouped by a recursive median split into clusters of at most 16
 // spheres, and consecutive clusters into groups of at most 8; both levels carry an axis-aligned
@@ -80,11 +82,11 @@ struct alignas(16) CollConsts {
   float4 sph[MAXS];              // local centre, radius
   float4 link_bs[MAXJ];          // link bounding sphere: local centre, radius (inflated); w < 0: none
   float4 point_sph;              // sphere family: offset and radius of the point robot
-  float4 clus_lo[MAXC];          // cluster box: lower corner (xyz)
-  float4 clus_hi[MAXC];          // cluster box: upper corner (xyz)
+  // boxes: lower and upper corner (xyz) in turn; the lane-per-configuration check reads four at a time (empty boxes follow
+  // the last), and a cluster's obstacle count stands in the w of its lower corner (as an integer's bits)
+  float4 clus_box[2 * MAXC];
   int2 clus_range[MAXC];         // obstacle index range of each cluster
-  float4 sup_lo[MAXSUP];         // group box: lower corner
-  float4 sup_hi[MAXSUP];         // group box: upper corner
+  float4 sup_box[2 * MAXSUP];    // groups of kGroupSize clusters
   int2 sup_range[MAXSUP];        // cluster index range of each group
 };
 
@@ -112,6 +114,7 @@ struct DevProblem {
   Consts c;
   CollConsts k;
   const float4* obs;             // obstacles (x, y, z, r), grouped by cluster, n_obs of them
+  const float4* obs_pad;         // the same, kClusterSize slots per cluster (spheres out of reach fill them up)
   unsigned long long* fallback_counter;
 };
 
@@ -209,6 +212,14 @@ __device__ __forceinline__ const CollConsts& coll_of(const DevProblem* P) {
 __device__ __forceinline__ const float4* obs_of(const DevProblem* P) {
   using PT = const float4* const __attribute__((address_space(4)));
   const float4* o = *(PT*)uniform_ptr(&P->obs);
+  using OT = const __attribute__((address_space(4))) float4;
+  OT* oc = (OT*)uniform_ptr(o);
+  return (const float4*)oc;
+}
+// The obstacle slots of the clusters, kClusterSize each, as scalar-load memory.
+__device__ __forceinline__ const float4* obs_pad_of(const DevProblem* P) {
+  using PT = const float4* const __attribute__((address_space(4)));
+  const float4* o = *(PT*)uniform_ptr(&P->obs_pad);
   using OT = const __attribute__((address_space(4))) float4;
   OT* oc = (OT*)uniform_ptr(o);
   return (const float4*)oc;

@@ -60,9 +60,9 @@ struct ProjArgs {
   int32_t* chk_idx;
   double* chk_q;
   int32_t n_sph, n_obs;   // robot and obstacle spheres (LDS size of the exact-check kernel)
-  int32_t chk_lanes;      // exact-check tail: lanes per queued configuration (0: by queue length; 1, 2, 4, 8, 16, 64)
-  int32_t chk_long;       // exact-check tail: lanes per configuration on a long queue with chk_lanes = 0
-                          // (1, 2, 4, 8 or 16; 0 = kTailCheckLanesLong)
+  int32_t chk_lanes;      // exact-check tail: lanes per queued configuration (0: the tuned choice; 1, 2, 4, 8, 16, 64)
+  int32_t chk_long;       // exact-check tail: lanes per configuration as tuned, with chk_lanes = 0 (2, 4, 8 or 16 on long
+                          // queues; 0 or 1: one lane per configuration on every queue)
 };
 
 constexpr int ST_DEFER = -2;  // internal: continue this configuration with FP64 steps
@@ -601,20 +601,50 @@ k_project_persistent(ProjArgs) {
   persistent_body<Model, IO, S, MODE, kTrigTile<Model, S, MODE>>(smem);
 }
 
-// Exact collision check of the configurations queued by k_project_persistent, L lanes per
-// configuration (grid-stride over the queue). A short queue (at most `small` entries: latency-bound,
-// few waves) runs a wave per configuration, each configuration's links split over up to 4 waves; a
-// longer one runs groups of chk_long lanes (the autotuner's choice among 1, 2, 4, 8 and 16; 4 by
-// default). Every lane of a group walks the tree, and the group splits the sphere-obstacle tests of
+// Exact collision check of the configurations queued by k_project_persistent: one configuration per lane, a work item per
+// 64 queued configurations and link (grid-stride). A lane group per configuration walked the whole tree in every lane of
+// the group and its wave ran the union of its groups' pair lists, every box and obstacle a vector operand; here a link's
+// chain is walked once per configuration and the scene is read into scalar registers. Bound by instruction issue where
+// most clusters are near, by the latency of the scalar reads else (four waves per SIMD: a chain's
+// coordinates, read at once, take 107 registers; five or more spill).
+// Before (groups of 4 lanes) and after, us: 65,536 humanoid configurations 26.5 -> 17.0, Digit 149 -> 107, 65,536 checked
+// humanoid configurations near the shelves 156 -> 106, 4,000 dual-arm geodesics of 4 to 128 configurations 349 -> 197,
+// 131,072 arm configurations 114 -> 55, 1,021 arm geodesics of 4 to 64 configurations 79 -> 36.
+template <class Model>
+__global__ void __launch_bounds__(256, 4) k_check_lanes(ProjArgs a) {
+  const int64_t cnt = *a.chk_count;
+  constexpr int NL = Model::NGEO;
+  const int lane = int(threadIdx.x) & 63;
+  const int wpb = int(blockDim.x) >> 6;
+  const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
+  const int64_t items = (cnt + 63) / 64 * NL;
+  for (int64_t item = int64_t(blockIdx.x) * wpb + wave; item < items; item += int64_t(gridDim.x) * wpb) {
+    const int64_t grp = item / NL;
+    const int64_t slot = grp * 64 + lane;
+    const bool in = slot < cnt;
+    const int64_t s = in ? slot : cnt - 1;
+    const int64_t i = a.chk_idx[s];
+    const bool live = in && a.verdict[i] != V_HIT;  // another link may have hit already
+    if (!__any(live)) continue;
+    const QGlob<double> q{a.chk_q, a.defer_cap, s, Model::D};
+    Rig<float> X;
+    const int l = Model::geo_frame(int(item - grp * NL), q, consts_of(a.P), X);
+    if (Model::link_hits(X, l, coll_of(a.P), obs_pad_of(a.P), live) && live) a.verdict[i] = V_HIT;  // queued as V_FREE
+  }
+}
+
+// The same check with groups of L lanes per configuration: the autotuner's alternatives on long queues (chk_long, 2
+// to 16 lanes), and what a caller may force (chk_lanes, 2 to 64).
+// Every lane of a group walks the tree, and the group splits the sphere-obstacle tests of
 // the (link, cluster) pairs it finds overlapping: smaller groups repeat fewer walks, but the lanes of
 // a wave then run different pair lists and the wave runs their union, so the best size depends on
-// the batch. A caller may force 1, 2, 4, 8, 16 or 64 lanes (chk_lanes).
+// the batch. 64 lanes: a wave per configuration, on short queues (at most `small` entries) each
+// configuration's links split over up to 4 waves.
 // Dynamic LDS: one configuration per lane group (D doubles each; a wave per configuration also
 // keeps 64 candidate-sphere slots per wave), then the robot spheres and the obstacles (float4
-// each); groups below 4 lanes exist for families of at most kTailCheckLowLanesMaxD
+// each); groups of 2 exist for families of at most kTailCheckLowLanesMaxD
 // coordinates and run only where their staged configurations leave room for 4 workgroups per CU
 // (min_lanes, from the launcher).
-constexpr int kTailCheckLanesLong = 4;
 constexpr int kTailCheckLowLanesMaxD = 16;
 constexpr size_t kTailCheckLdsBudget = 40 * 1024;  // a quarter of a CU's LDS
 
@@ -648,7 +678,7 @@ template <class Model, class IO>
 __global__ void __launch_bounds__(256) k_check_tail(ProjArgs a, int64_t small, int min_lanes) {
   extern __shared__ double smem[];
   const int64_t cnt = *a.chk_count;
-  int L = a.chk_lanes != 0 ? a.chk_lanes : cnt <= small ? 64 : a.chk_long > 0 ? a.chk_long : kTailCheckLanesLong;
+  int L = a.chk_lanes != 0 ? a.chk_lanes : cnt <= small ? 64 : a.chk_long;
   if (L < min_lanes) L = min_lanes;
   if (L == 64) {
     check_tail_body<Model, IO, 64>(a, small, cnt, smem);
@@ -657,8 +687,7 @@ __global__ void __launch_bounds__(256) k_check_tail(ProjArgs a, int64_t small, i
   } else if (L == 8) {
     check_tail_body<Model, IO, 8>(a, small, cnt, smem);
   } else if constexpr (Model::D <= kTailCheckLowLanesMaxD) {
-    if (L == 1) check_tail_body<Model, IO, 1>(a, small, cnt, smem);
-    else if (L == 2) check_tail_body<Model, IO, 2>(a, small, cnt, smem);
+    if (L == 2) check_tail_body<Model, IO, 2>(a, small, cnt, smem);
     else check_tail_body<Model, IO, 4>(a, small, cnt, smem);
   } else {
     check_tail_body<Model, IO, 4>(a, small, cnt, smem);

@@ -420,6 +420,42 @@ struct Kin {
     return r;
   }
 
+  // Frame X of joint j from its parent's frame B (not read where the parent is the world).
+  template <class T, int j>
+  static __device__ __forceinline__ void joint_frame(const Rig<T>& B, const JP<T>& cur, Rig<T>& X) {
+    constexpr int par = Topo::parent[j];
+    constexpr int ax = Topo::axis[j];
+    if constexpr (par < 0) {
+      if constexpr (Topo::origin_rot) {
+        for (int k = 0; k < 9; ++k) X.R[k] = cur.R[k];
+      } else {
+        for (int k = 0; k < 9; ++k) X.R[k] = (k % 4 == 0) ? T(1) : T(0);
+      }
+      for (int k = 0; k < 3; ++k) X.p[k] = cur.p[k];
+    } else {
+      if constexpr (Topo::origin_rot) {
+        matmul3(B.R, cur.R, X.R);
+      } else {
+        for (int k = 0; k < 9; ++k) X.R[k] = B.R[k];
+      }
+      T t[3];
+      matvec3(B.R, cur.p, t);
+      for (int k = 0; k < 3; ++k) X.p[k] = B.p[k] + t[k];
+    }
+    if constexpr (Topo::jtype[j] == PRI) {
+      for (int r = 0; r < 3; ++r) X.p[r] += X.R[3 * r + ax] * cur.q;
+    } else {
+      T s, c;
+      sincos_t(cur.q, &s, &c);
+      constexpr int i = (ax + 1) % 3, k = (ax + 2) % 3;
+      for (int r = 0; r < 3; ++r) {
+        const T a = X.R[3 * r + i], b = X.R[3 * r + k];
+        X.R[3 * r + i] = a * c + b * s;
+        X.R[3 * r + k] = b * c - a * s;
+      }
+    }
+  }
+
   // Forward kinematics, streaming each link frame to visit(ic<j>, frame, joint data) in joint
   // order. Joint j+1's data is read while joint j is computed; with ORDERED, joint j+1's read
   // is ordered after joint j-1's frame, so the walk keeps one joint of data in flight (register
@@ -432,7 +468,6 @@ struct Kin {
     sfor<0, NJ>([&](auto J) {
       constexpr int j = decltype(J)::value;
       constexpr int par = Topo::parent[j];
-      constexpr int ax = Topo::axis[j];
       JP<T> nxt;  // the next joint's data, requested one joint ahead
       if constexpr (j + 1 < NJ) {
         if constexpr (!ORDERED) nxt = load_joint<T, j + 1>(q, P, 0);
@@ -440,36 +475,7 @@ struct Kin {
         else nxt = load_joint<T, j + 1>(q, P, cur.q);
       }
       Rig<T>& X = L[j];
-      if constexpr (par < 0) {
-        if constexpr (Topo::origin_rot) {
-          for (int k = 0; k < 9; ++k) X.R[k] = cur.R[k];
-        } else {
-          for (int k = 0; k < 9; ++k) X.R[k] = (k % 4 == 0) ? T(1) : T(0);
-        }
-        for (int k = 0; k < 3; ++k) X.p[k] = cur.p[k];
-      } else {
-        const Rig<T>& B = L[par];
-        if constexpr (Topo::origin_rot) {
-          matmul3(B.R, cur.R, X.R);
-        } else {
-          for (int k = 0; k < 9; ++k) X.R[k] = B.R[k];
-        }
-        T t[3];
-        matvec3(B.R, cur.p, t);
-        for (int k = 0; k < 3; ++k) X.p[k] = B.p[k] + t[k];
-      }
-      if constexpr (Topo::jtype[j] == PRI) {
-        for (int r = 0; r < 3; ++r) X.p[r] += X.R[3 * r + ax] * cur.q;
-      } else {
-        T s, c;
-        sincos_t(cur.q, &s, &c);
-        constexpr int i = (ax + 1) % 3, k = (ax + 2) % 3;
-        for (int r = 0; r < 3; ++r) {
-          const T a = X.R[3 * r + i], b = X.R[3 * r + k];
-          X.R[3 * r + i] = a * c + b * s;
-          X.R[3 * r + k] = b * c - a * s;
-        }
-      }
+      joint_frame<T, j>(L[par < 0 ? 0 : par], cur, X);
       visit(J, X, cur);
       if constexpr (j + 1 < NJ) cur = nxt;
     });
@@ -925,8 +931,8 @@ struct Kin {
     sfor<0, PB>([&](auto BI) {
       constexpr int bi = decltype(BI)::value;
       const int c = bi * L + t;
-      blo[bi] = c < ncl ? K.clus_lo[c] : make_float4(1e30f, 1e30f, 1e30f, 0.f);  // empty box
-      bhi[bi] = c < ncl ? K.clus_hi[c] : make_float4(-1e30f, -1e30f, -1e30f, 0.f);
+      blo[bi] = c < ncl ? K.clus_box[2 * c] : make_float4(1e30f, 1e30f, 1e30f, 0.f);  // empty box
+      bhi[bi] = c < ncl ? K.clus_box[2 * c + 1] : make_float4(-1e30f, -1e30f, -1e30f, 0.f);
     });
     bool hit = false;
     fk<float, false>(q, P.f, [&](auto J, const Rig<float>& X, const JP<float>&) {
@@ -951,7 +957,7 @@ struct Kin {
               // the obstacle spheres with a margin far above FP32 rounding, so a sphere farther
               // than its radius from it overlaps none of them); the group's lanes split the
               // obstacles of the spheres that pass
-              const float4 clo = K.clus_lo[cc], chi = K.clus_hi[cc];
+              const float4 clo = K.clus_box[2 * cc], chi = K.clus_box[2 * cc + 1];
               for (int si = 0; si < ns; ++si) {
                 const float4 sp = sph[s0 + si];
                 const float lp[3] = {sp.x, sp.y, sp.z};
@@ -970,7 +976,7 @@ struct Kin {
               // a wave per configuration: lane t transforms sphere t and tests it against the
               // cluster's box; the candidates' centres go to the wave's LDS slots in rank order
               // and the lanes split the (candidate, obstacle) pairs
-              const float4 clo = K.clus_lo[cc], chi = K.clus_hi[cc];
+              const float4 clo = K.clus_box[2 * cc], chi = K.clus_box[2 * cc + 1];
               bool cand = false;
               float4 cs = make_float4(0.f, 0.f, 0.f, 0.f);
               if (t < ns) {
@@ -1030,10 +1036,10 @@ struct Kin {
             // first, then against the clusters of the groups it reaches (a group's box contains its
             // clusters' boxes, in FP32 too, so no overlapping cluster is skipped)
             for (int g = 0; g < K.n_sup; ++g) {
-              if (box_dist2(cb, K.sup_lo[g], K.sup_hi[g]) > r2) continue;
+              if (box_dist2(cb, K.sup_box[2 * g], K.sup_box[2 * g + 1]) > r2) continue;
               const int2 gr = K.sup_range[g];
               for (int c = gr.x; c < gr.y; ++c)
-                if (box_dist2(cb, K.clus_lo[c], K.clus_hi[c]) <= r2) pairs(c, K.clus_range[c]);
+                if (box_dist2(cb, K.clus_box[2 * c], K.clus_box[2 * c + 1]) <= r2) pairs(c, K.clus_range[c]);
             }
             return;
           }
@@ -1046,12 +1052,115 @@ struct Kin {
           for (int b = 0; b < nbp; ++b) process(b, (own >> b) & 1u);
           for (int b = PB; b < nb; ++b) {  // clusters beyond the register-resident ones
             const int c = b * L + t;
-            process(b, c < ncl && box_dist2(cb, K.clus_lo[c], K.clus_hi[c]) <= r2);
+            process(b, c < ncl && box_dist2(cb, K.clus_box[2 * c], K.clus_box[2 * c + 1]) <= r2);
           }
         }
       }
     });
     return ((uint64_t(__ballot(hit)) >> shift) & gmask) != 0;
+  }
+
+  // Frame of link l alone: its chain from the root.
+  template <int l, class Q>
+  static __device__ __forceinline__ void chain_frame(const Q& q, const TP<float>& P, Rig<float>& X) {
+    Rig<float> B;
+    if constexpr (Topo::parent[l] >= 0) chain_frame<Topo::parent[l]>(q, P, B);
+    joint_frame<float, l>(B, load_joint<float, l>(q, P, 0), X);
+  }
+  // Frame and index of the link of rank r among the links that may carry spheres (r wave-uniform).
+  template <class Q>
+  static __device__ __forceinline__ int geo_frame(int r, const Q& q, const Consts& P, Rig<float>& X) {
+    int link = 0;
+    sfor<0, NJ>([&](auto J) {
+      constexpr int l = decltype(J)::value;
+      if constexpr (Topo::may_have_spheres(l)) {
+        if (r == geo_rank(l)) {
+          chain_frame<l>(q, P.f, X);
+          link = l;
+        }
+      }
+    });
+    return link;
+  }
+
+  // Collision check of one link, one configuration per lane. Everything but the configuration is wave-uniform: the
+  // link's bound is tested against the boxes of the cluster groups and of their clusters, four boxes per scalar read,
+  // and a cluster that any lane's link reaches is taken for the whole wave, its box and all its obstacles read at once
+  // into scalar registers and tested against the link's spheres four at a time. Lanes that did not need a test run
+  // it all the same: an overlap it finds is one. (The queue keeps neighbouring configurations of a geodesic in
+  // neighbouring lanes, whose clusters are mostly the same.)
+  static __device__ __forceinline__ bool link_hits(const Rig<float>& X, int l, const CollConsts& K, const float4* pad, bool live) {
+    using V16 = float __attribute__((ext_vector_type(16), aligned(16)));
+    using V8 = float __attribute__((ext_vector_type(8), aligned(16)));
+    const float4 bs = K.link_bs[l];
+    const int s0 = K.sph_begin[l], s1 = K.sph_begin[l + 1];
+    if (bs.w < 0.f) return false;
+    const float lc[3] = {bs.x, bs.y, bs.z};
+    float cb[3];
+    matvec3(X.R, lc, cb);
+    for (int k = 0; k < 3; ++k) cb[k] += X.p[k];
+    const float r2 = bs.w * bs.w;
+    auto reach = [&](const V16& v, int k) {  // box k of the two in v
+      const float4 lo = make_float4(v[8 * k], v[8 * k + 1], v[8 * k + 2], 0.f);
+      const float4 hi = make_float4(v[8 * k + 4], v[8 * k + 5], v[8 * k + 6], 0.f);
+      return __any(live && box_dist2(cb, lo, hi) <= r2);
+    };
+    uint64_t near0 = 0, near1 = 0;  // clusters that some lane's link reaches
+    uint32_t groups = 0;
+    for (int g = 0; g < K.n_sup; g += 4) {
+      const V16 a = *(const V16*)(K.sup_box + 2 * g), b = *(const V16*)(K.sup_box + 2 * g + 4);
+      const uint32_t m = uint32_t(reach(a, 0)) | uint32_t(reach(a, 1)) << 1 | uint32_t(reach(b, 0)) << 2 | uint32_t(reach(b, 1)) << 3;
+      groups |= m << g;
+    }
+    while (groups != 0) {
+      const int g = __builtin_ctz(groups);
+      groups &= groups - 1;
+      for (int h = 0; h < kGroupSize; h += 4) {
+        const int c = g * kGroupSize + h;
+        const V16 a = *(const V16*)(K.clus_box + 2 * c), b = *(const V16*)(K.clus_box + 2 * c + 4);
+        const uint64_t m = uint64_t(reach(a, 0)) | uint64_t(reach(a, 1)) << 1 | uint64_t(reach(b, 0)) << 2 | uint64_t(reach(b, 1)) << 3;
+        if (c < 64) near0 |= m << c;
+        else near1 |= m << (c - 64);
+      }
+    }
+    bool hit = false;
+    for (int s = s0; s < s1 && (near0 | near1) != 0; s += 4) {
+      float c[4][3], r[4];
+      for (int k = 0; k < 4; ++k) {  // the last group repeats the link's last sphere
+        const float4 sp = K.sph[s + k < s1 ? s + k : s1 - 1];
+        const float lp[3] = {sp.x, sp.y, sp.z};
+        matvec3(X.R, lp, c[k]);
+        for (int x = 0; x < 3; ++x) c[k][x] += X.p[x];
+        r[k] = sp.w;
+      }
+      uint64_t m0 = near0, m1 = near1;
+      while ((m0 | m1) != 0) {
+        const int cc = m0 != 0 ? __builtin_ctzll(m0) : 64 + __builtin_ctzll(m1);
+        if (m0 != 0) m0 &= m0 - 1;
+        else m1 &= m1 - 1;
+        const V8 bx = *(const V8*)(K.clus_box + 2 * cc);
+        const float4* po = pad + cc * kClusterSize;
+        const V16 ob[4] = {*(const V16*)po, *(const V16*)(po + 4), *(const V16*)(po + 8), *(const V16*)(po + 12)};
+        const int count = __float_as_int(bx[3]);
+        const float4 lo = make_float4(bx[0], bx[1], bx[2], 0.f), hi = make_float4(bx[4], bx[5], bx[6], 0.f);
+        sfor<0, 4>([&](auto SK) {
+          constexpr int k = decltype(SK)::value;
+          if (!__any(live && !hit && box_dist2(c[k], lo, hi) <= r[k] * r[k])) return;
+          sfor<0, kClusterSize / 4>([&](auto V) {
+            constexpr int v = decltype(V)::value;
+            if (4 * v < count) {
+              sfor<0, 4>([&](auto O) {
+                constexpr int o = 4 * decltype(O)::value;
+                const float dx = c[k][0] - ob[v][o], dy = c[k][1] - ob[v][o + 1], dz = c[k][2] - ob[v][o + 2];
+                const float rr = r[k] + ob[v][o + 3];
+                hit = hit || (dx * dx + dy * dy + dz * dz < rr * rr);
+              });
+            }
+          });
+        });
+      }
+    }
+    return hit;
   }
 
   // Broad-phase flag of one configuration: does the bounding sphere of some link reach into the

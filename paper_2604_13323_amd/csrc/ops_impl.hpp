@@ -61,26 +61,28 @@ hipError_t OpsImpl<Model, IO, S>::project_tail(const ProjArgs& a, int grid, hipS
 }
 template <class Model, class IO, class S>
 hipError_t OpsImpl<Model, IO, S>::check_tail(const ProjArgs& a, int grid, hipStream_t s) {
-  const size_t stage = size_t(a.n_sph + a.n_obs) * 16;
-  // short queues: a wave (or part of one configuration's links) per work item, one pass of
-  // `small` work items over 4 waves per workgroup
-  const int64_t small = int64_t(grid) * 4;
-  // the smallest lane group whose staged configurations fit beside the spheres in a quarter of the
-  // CU's LDS; the LDS covers 256 / min_lanes groups (or the wave path's slots, if more)
-  int min_lanes = 4;
-  if constexpr (Model::D <= kTailCheckLowLanesMaxD) {
-    for (int L = 1; L < 4; L *= 2)
-      if (size_t(256 / L) * Model::D * sizeof(double) + stage <= kTailCheckLdsBudget) {
-        min_lanes = L;
-        break;
-      }
+  if constexpr (!Model::broad_in_residual) {
+    return hipErrorInvalidValue;  // not in the launch table of such a model
+  } else {
+    if (a.chk_lanes == 1 || (a.chk_lanes == 0 && a.chk_long <= 1)) {
+      hipLaunchKernelGGL((k_check_lanes<Model>), dim3(grid), dim3(256), 0, s, a);
+      return hipGetLastError();
+    }
+    const size_t stage = size_t(a.n_sph + a.n_obs) * 16;
+    // short queues: a wave (or part of one configuration's links) per work item, one pass of
+    // `small` work items over 4 waves per workgroup
+    const int64_t small = int64_t(grid) * 4;
+    // groups of 2 lanes only where their staged configurations fit beside the spheres in a quarter of the
+    // CU's LDS; the LDS covers 256 / min_lanes groups (or the wave path's slots, if more)
+    int min_lanes = 4;
+    if (Model::D <= kTailCheckLowLanesMaxD && size_t(256 / 2) * Model::D * sizeof(double) + stage <= kTailCheckLdsBudget) min_lanes = 2;
+    // the wave-per-configuration path: 4 configurations and 4 x 64 candidate slots (float4)
+    const size_t cols64 = size_t(4) * Model::D * sizeof(double) + size_t(4) * 64 * 16;
+    const size_t cols_l = size_t(256 / min_lanes) * Model::D * sizeof(double);
+    const size_t cols = cols_l > cols64 ? cols_l : cols64;
+    hipLaunchKernelGGL((k_check_tail<Model, IO>), dim3(grid), dim3(256), cols + stage, s, a, small, min_lanes);
+    return hipGetLastError();
   }
-  // the wave-per-configuration path: 4 configurations and 4 x 64 candidate slots (float4)
-  const size_t cols64 = size_t(4) * Model::D * sizeof(double) + size_t(4) * 64 * 16;
-  const size_t cols_l = size_t(256 / min_lanes) * Model::D * sizeof(double);
-  const size_t cols = cols_l > cols64 ? cols_l : cols64;
-  hipLaunchKernelGGL((k_check_tail<Model, IO>), dim3(grid), dim3(256), cols + stage, s, a, small, min_lanes);
-  return hipGetLastError();
 }
 template <class Model, class IO, class S>
 hipError_t OpsImpl<Model, IO, S>::vjp_tail(const VjpArgs& a, int grid, hipStream_t s) {

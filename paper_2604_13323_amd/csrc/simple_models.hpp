@@ -22,10 +22,10 @@ __device__ __forceinline__ void point_check(const float* c, float r, const CollC
     }
   } else {
     for (int g = 0; g < K.n_sup; ++g) {
-      if (!__any(!hit && box_dist2(c, K.sup_lo[g], K.sup_hi[g]) <= r * r)) continue;  // wave-uniform
+      if (!__any(!hit && box_dist2(c, K.sup_box[2 * g], K.sup_box[2 * g + 1]) <= r * r)) continue;  // wave-uniform
       const int2 cr = K.sup_range[g];
       for (int k = cr.x; k < cr.y; ++k) {
-        if (!hit && box_dist2(c, K.clus_lo[k], K.clus_hi[k]) <= r * r) {
+        if (!hit && box_dist2(c, K.clus_box[2 * k], K.clus_box[2 * k + 1]) <= r * r) {
           const int2 rg = K.clus_range[k];
           for (int o = rg.x; o < rg.y; ++o) {
             const float4 ob = obs[o];
