@@ -442,6 +442,16 @@ struct Direct {
   static __device__ __forceinline__ double residual(const Q& q, const Consts& C, S* F, SD<S>& sd, const TR&) {
     return Model::template residual<S, RM>(q, C, F, sd);
   }
+  struct Basis {};  // the rows are the scene's own
+  template <class Q, class TR>
+  static __device__ __forceinline__ void residual_basis(const Q& q, const Consts& C, double* F, SD<double>& sd, Basis&, const TR&) {
+    Model::template residual<double>(q, C, F, sd);
+  }
+  template <bool FORWARD, class TR>
+  static __device__ __forceinline__ void change_rows(const Basis&, const TR&, double*) {}
+  static __device__ __forceinline__ void freeze_rows(SD<double>& sd, const SD<double>& base) {
+    if constexpr (Model::DROPPABLE != 0) Model::freeze_rows(sd, base);
+  }
   template <class S, class Q, class TR>
   static __device__ __forceinline__ void step_data(const Q& q, const Consts& C, SD<S>& sd, const TR&) {
     S F[Model::M];

@@ -1013,6 +1013,11 @@ struct FLds {
   LP base;
   __device__ __forceinline__ float operator[](int j) const { return base[j * 64]; }
   __device__ __forceinline__ void set(int j, float v) const { base[j * 64] = v; }
+  __device__ __forceinline__ FLds fresh() const {
+    FLds r = *this;
+    asm volatile("" : "+v"(r.base));
+    return r;
+  }
 };
 // Sink of a J^T c walk that hands (j, value) to a callable.
 template <class S, class Fn>
@@ -1035,61 +1040,85 @@ struct QShift {
   __device__ __forceinline__ double at(int j) const { return q.at(j) + t * double(u[j]); }
   template <class U>
   __device__ __forceinline__ double at(int j, U dep) const { return q.at(j, dep) + t * double(u[j]); }
+  __device__ __forceinline__ double get(int j) const { return q.get(j) + t * double(u[j]); }
+  __device__ __forceinline__ QShift fresh() const { return QShift{q.fresh(), u.fresh(), t}; }
 };
 
-// FP64 Gram of J J^T + lambda I at q, factorised; false when it is not positive definite.
-template <class Model>
-__device__ __forceinline__ bool gram64(const QLds& q, const Consts& C, double lambda,
-                                       typename Model::template SD<double>& sd, double* F, double* G, double* invd) {
+// FP64 Gram of J J^T + lambda I at q, factorised (and v = J g, where asked for); false when it is not positive definite.
+template <class Model, bool WITH_V, class TR, class GV>
+__device__ __forceinline__ bool gram64(const QLds& q, const TR& tr, const Consts& C, double lambda,
+                                       typename StepOf<Model>::type::template SD<double>& sd, typename StepOf<Model>::type::Basis& bs,
+                                       double* F, double* G, double* invd, GV g, double* v) {
   constexpr int M = Model::M;
-  Model::template residual<double>(q, C, F, sd);
-  Model::template gram<double, false>(q, C, sd, G, (const double*)nullptr, (double*)nullptr);
+  using W = typename StepOf<Model>::type;
+  W::residual_basis(q, C, F, sd, bs, tr);
+  if constexpr (WITH_V) W::template gram_jv<double>(q, C, sd, tr, G, g, v);
+  else W::template gram<double>(q, C, sd, tr, G);
+  if (lambda > 0.0) W::template add_lambda<double>(G, F, lambda, tr);
   double maxd = 0.0, kappa;
-  for (int r = 0; r < M; ++r) {
-    G[pidx(r, r)] += lambda;
-    maxd = fmax(maxd, G[pidx(r, r)]);
-  }
+  for (int r = 0; r < M; ++r) maxd = fmax(maxd, G[pidx(r, r)]);
   return cholesky<Model, double>(G, invd, kappa, kFloorF64 * maxd, drop_bits<Model>(sd));
 }
 
-// k FP64 Newton steps from the input (replaying the forward pass's path); false on a failure.
-template <class Model, class IO>
-__device__ __forceinline__ bool replay(const VjpxArgs& a, int dof, int64_t i, int k, const QLds& q, const Consts& C) {
+// k FP64 Newton steps from the input (replaying the forward pass's path); false on a failure. The loop runs as long as
+// any lane has steps left, so the constants' scalar addresses stay wave-uniform over it.
+template <class Model, class IO, class TR>
+__device__ __forceinline__ bool replay(const VjpxArgs& a, int dof, int64_t i, int k, const QLds& q, const TR& tr, const Consts& C) {
   constexpr int M = Model::M;
+  using W = typename StepOf<Model>::type;
   const IO* p = static_cast<const IO*>(a.q_in) + i;
   for (int c = 0; c < Model::D; ++c) q.set(c, c < dof ? double(p[int64_t(c) * a.ld]) : 0.0);
-  for (int s = 0; s < k; ++s) {
-    typename Model::template SD<double> sd;
+  bool ok = true;
+  for (int s = 0; __any(ok && s < k); ++s) {
+    if (!(ok && s < k)) continue;
+    typename W::template SD<double> sd;
+    typename W::Basis bs;
     double F[M], G[M * (M + 1) / 2], invd[M];
-    if (!gram64<Model>(q, C, a.lambda, sd, F, G, invd)) return false;
+    if (!gram64<Model, false>(q, tr, C, a.lambda, sd, bs, F, G, invd, (const double*)nullptr, (double*)nullptr)) {
+      ok = false;
+      continue;
+    }
     chol_solve<Model, double>(G, invd, F);
     const double al = a.alpha;
-    // the walk has read coordinate j when it reports column j, so the update can go in place
-    Model::template jty<double>(q, C, sd, F, fn_sink<double>([&](int j, double acc) { q.set(j, q.at(j) - al * acc); }));
+    // a walk has read coordinate j when it reports column j, so the update can go in place
+    W::template jty<double>(q, C, sd, tr, F, fn_sink<double>([&](int j, double acc) { q.set(j, q.get(j) - al * acc); }));
   }
-  return true;
+  return ok;
 }
 
 // Accumulate coef * (gradient of c.F at q + t u/|u|) into w (the FP64 cotangent tile: the two
-// evaluations of a central difference add nearly cancelling terms of size |u| |grad| / 2h).
+// evaluations of a central difference add nearly cancelling terms of size |u| |grad| / 2h). c in the scene's rows.
 // Rows that a lane may drop keep the base point's choice (base: the step data at q).
-template <class Model>
-__device__ __forceinline__ void grad_axpy(const QLds& q, const FLds& u, double t, const Consts& C, const double* c,
-                                          double coef, const QLds& w, const typename Model::template SD<double>& base) {
+template <class Model, class TR>
+__device__ __forceinline__ void grad_axpy(const QLds& q, const FLds& u, double t, const TR& tr, const double* c,
+                                          double coef, const QLds& w,
+                                          const typename StepOf<Model>::type::template SD<double>& base) {
   constexpr int M = Model::M;
+  using W = typename StepOf<Model>::type;
+  const Consts& C = consts_of(kernarg<VjpxArgs>().P);
   const QShift qs{q, u, t};
-  typename Model::template SD<double> sd;
-  double F[M];
-  Model::template residual<double>(qs, C, F, sd);
-  if constexpr (Model::DROPPABLE != 0) Model::freeze_rows(sd, base);
-  Model::template jty<double>(qs, C, sd, c, fn_sink<double>([&](int j, double acc) { w.set(j, w.at(j) + coef * acc); }));
+  typename W::template SD<double> sd;
+  typename W::Basis bs;
+  double F[M], y[M];
+  W::residual_basis(qs, C, F, sd, bs, tr);
+  W::freeze_rows(sd, base);
+  for (int r = 0; r < M; ++r) y[r] = c[r];
+  W::template change_rows<true>(bs, tr, y);
+  W::template jty<double>(qs, C, sd, tr, y, fn_sink<double>([&](int j, double acc) { w.set(j, w.get(j) + coef * acc); }));
 }
 
+// Bound by FP64 instruction issue (one wave per SIMD, K <= 3 steps on the batches that use it: K (K - 1) / 2 + 1
+// replayed steps and ten walks per reverse step). On walks that re-formed world-axis columns from the root, with the
+// moments' prefix sums and 1.7 KB of spills per lane, it took 597 us for 18,530 humanoid configurations;
+// on the leaf-to-root walks 411 us.
+// Dynamic LDS: the sine table, per wave two FP64 tiles (iterate, cotangent) and an FP32 one (direction).
 template <class Model, class IO>
 __global__ void __launch_bounds__(64) k_vjp_exact(VjpxArgs a) {
   constexpr int D = Model::D, M = Model::M;
+  using W = typename StepOf<Model>::type;
   extern __shared__ double smem[];
   const Consts& C = consts_of(a.P);
+  const auto tr = make_trig<Model, false>(smem, nullptr);
   const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
   if (i >= a.n) return;
   const int dof = dof_of<Model>(C);
@@ -1099,67 +1128,77 @@ __global__ void __launch_bounds__(64) k_vjp_exact(VjpxArgs a) {
     return;
   }
   // tiles: the FP64 iterate and cotangent w (waves' tiles in turn), then the FP32 direction v (a, then delta)
+  double* tiles = smem + kTabDoubles<Model>;
   const int nw = int(blockDim.x) >> 6, w0 = int(threadIdx.x) >> 6, l = int(threadIdx.x) & 63;
-  const QLds q{(QLds::LP)(smem + w0 * (D * 64) + l)};
-  const QLds w{(QLds::LP)(smem + (nw + w0) * (D * 64) + l)};
-  float* fb = reinterpret_cast<float*>(smem + 2 * nw * (D * 64));
+  const QLds q{(QLds::LP)(tiles + w0 * (D * 64) + l)};
+  const QLds w{(QLds::LP)(tiles + (nw + w0) * (D * 64) + l)};
+  float* fb = reinterpret_cast<float*>(tiles + 2 * nw * (D * 64));
   const FLds v{(FLds::LP)(fb + w0 * (D * 64) + l)};
   const int K = a.iters[i];
-  bool ok = replay<Model, IO>(a, dof, i, K, q, C);
+  bool ok = replay<Model, IO>(a, dof, i, K, q, tr, C);
   {
     const IO* pg = static_cast<const IO*>(a.g) + i;
     for (int c = 0; c < D; ++c) w.set(c, c < dof ? double(pg[int64_t(c) * a.ld]) : 0.0);
   }
   // w <- (I - J^+ J) w at q_K
   if (ok) {
-    typename Model::template SD<double> sd;
+    typename W::template SD<double> sd;
+    typename W::Basis bs;
     double F[M], G[M * (M + 1) / 2], invd[M], z[M];
-    ok = gram64<Model>(q, C, 0.0, sd, F, G, invd);
+    ok = gram64<Model, true>(q, tr, C, 0.0, sd, bs, F, G, invd, w.fresh(), z);
     if (ok) {
-      Model::template jv<double>(q, C, sd, w, z);
       chol_solve<Model, double>(G, invd, z);
-      Model::template jty<double>(q, C, sd, z, fn_sink<double>([&](int j, double acc) { w.set(j, w.at(j) - acc); }));
+      W::template jty<double>(q, C, sd, tr, z, fn_sink<double>([&](int j, double acc) { w.set(j, w.get(j) - acc); }));
     }
   }
   for (int k = K - 1; k >= 0 && ok; --k) {
-    ok = replay<Model, IO>(a, dof, i, k, q, C);
+    ok = replay<Model, IO>(a, dof, i, k, q, tr, C);
     if (!ok) break;
-    typename Model::template SD<double> sd;
-    double F[M], G[M * (M + 1) / 2], invd[M], z[M];
-    ok = gram64<Model>(q, C, a.lambda, sd, F, G, invd);
-    if (!ok) break;
-    chol_solve<Model, double>(G, invd, F);  // F <- y
-    Model::template jv<double>(q, C, sd, w, z);
-    chol_solve<Model, double>(G, invd, z);  // z = G^-1 J w
+    typename W::template SD<double> sd;
+    typename W::Basis bs;
+    double F[M], z[M];
+    {
+      double G[M * (M + 1) / 2], invd[M];
+      ok = gram64<Model, true>(q, tr, C, a.lambda, sd, bs, F, G, invd, w.fresh(), z);
+      if (!ok) break;
+      chol_solve<Model, double>(G, invd, F);  // F <- y
+      chol_solve<Model, double>(G, invd, z);  // z = G^-1 J w
+    }
     const double al = a.alpha;
     // v <- a = w - J^T z, then w <- (1 - alpha) w + alpha a (= w - alpha J^T z)
-    Model::template jty<double>(q, C, sd, z, fn_sink<double>([&](int j, double acc) {
-      const double wj = w.at(j), aj = wj - acc;
+    W::template jty<double>(q, C, sd, tr, z, fn_sink<double>([&](int j, double acc) {
+      const double wj = w.get(j), aj = wj - acc;
       v.set(j, float(aj));
       w.set(j, (1.0 - al) * wj + al * aj);
     }));
     double qn = 1.0, vn = 0.0;
     for (int c = 0; c < D; ++c) {
-      qn = fmax(qn, fabs(q.at(c)));
+      qn = fmax(qn, fabs(q.get(c)));
       vn += double(v[c]) * double(v[c]);
     }
     const double h = a.h_rel * qn;
     vn = sqrt(vn);
+    // y and z in the scene's rows, which stay fixed where the gradients of y.F and z.F are differenced
+    double ys[M], zs[M];
+    for (int r = 0; r < M; ++r) {
+      ys[r] = F[r];
+      zs[r] = z[r];
+    }
+    W::template change_rows<false>(bs, tr, ys);
+    W::template change_rows<false>(bs, tr, zs);
     // w -= alpha H(y.F) a: central difference of the gradient J^T y along a / |a|, times |a| / 2h
     if (vn > 0.0) {
       const double coef = al * vn / (2.0 * h);
-      grad_axpy<Model>(q, v, h / vn, C, F, -coef, w, sd);
-      grad_axpy<Model>(q, v, -h / vn, C, F, coef, w, sd);
+      for (int sgn = 1; sgn >= -1; sgn -= 2) grad_axpy<Model>(q, v, sgn * h / vn, tr, ys, -sgn * coef, w, sd);
     }
     // v <- delta = J^T y, then w += alpha H(z.F) delta
-    Model::template jty<double>(q, C, sd, F, fn_sink<double>([&](int j, double acc) { v.set(j, float(acc)); }));
+    W::template jty<double>(q, C, sd, tr, F, fn_sink<double>([&](int j, double acc) { v.set(j, float(acc)); }));
     double dn = 0.0;
     for (int c = 0; c < D; ++c) dn += double(v[c]) * double(v[c]);
     dn = sqrt(dn);
     if (dn > 0.0) {
       const double coef = al * dn / (2.0 * h);
-      grad_axpy<Model>(q, v, h / dn, C, z, coef, w, sd);
-      grad_axpy<Model>(q, v, -h / dn, C, z, -coef, w, sd);
+      for (int sgn = 1; sgn >= -1; sgn -= 2) grad_axpy<Model>(q, v, sgn * h / dn, tr, zs, sgn * coef, w, sd);
     }
   }
   for (int c = 0; c < dof; ++c) out[int64_t(c) * a.ld] = ok ? IO(w.at(c)) : IO(__builtin_nan(""));

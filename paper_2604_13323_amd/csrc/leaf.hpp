@@ -146,6 +146,13 @@ struct Leaf {
     uint32_t drop = 0;
   };
 
+  // The change of row basis T at a point, for callers that need the scene's own rows (POSE rows with their linear part
+  // in the world's axes, REL rows in frame a's, both constant rotations of them): y' = T^T y.
+  struct Basis {
+    double R[NB][9];  // POSE: rotation of the end frame; REL: R_a^T R_b
+    double w[NB][3];
+  };
+
   // ---------------------------------------------------------------- joint data
   template <class T>
   struct JD {
@@ -428,7 +435,7 @@ struct Leaf {
   }
   template <int b, bool WITH_F, class S>
   static __device__ __forceinline__ void finish_block(Rig<double>* X, const BlockConsts& bc, S* F, double& n2, SD<S>& sd,
-                                                      double (*sc)[4]) {
+                                                      double (*sc)[4], Basis* basis) {
     constexpr int r0 = KI::brow0(b);
     Rig<double>& A = X[2 * b];
     static_assert(has_chain(2 * b) || is_dist(b), "a chain that ends where it starts: rods only");
@@ -458,6 +465,8 @@ struct Leaf {
           for (int k = 0; k < 9; ++k) sd.Rb[b][k] = to_step<S>(B.R[k]);
       }
       if constexpr (WITH_F) {
+        if (basis)
+          for (int k = 0; k < 9; ++k) basis->R[b][k] = Rr[k];
         // sin(theta) times the axis and cos(theta) of R_ref^T Rr, from the entries they need
         auto re = [&](int i, int k) { return Rt[3 * i] * Rr[k] + Rt[3 * i + 1] * Rr[3 + k] + Rt[3 * i + 2] * Rr[6 + k]; };
         sc[b][0] = 0.5 * (re(2, 1) - re(1, 2));
@@ -521,6 +530,12 @@ struct Leaf {
   static __device__ __forceinline__ double residual(const Q& q, const Consts& P, S* F, SD<S>& sd, const TR& tr) {
     return residual_pass<S, true>(q, P, F, sd, tr);
   }
+  // with the change of row basis
+  template <class Q, class TR>
+  static __device__ __forceinline__ void residual_basis(const Q& q, const Consts& P, double* F, SD<double>& sd, Basis& bs,
+                                                        const TR& tr) {
+    residual_pass<double, true>(q, P, F, sd, tr, &bs);
+  }
   // the step data alone
   template <class S, class Q, class TR>
   static __device__ __forceinline__ void step_data(const Q& q, const Consts& P, SD<S>& sd, const TR& tr) {
@@ -528,7 +543,8 @@ struct Leaf {
     residual_pass<S, false>(q, P, F, sd, tr);
   }
   template <class S, bool WITH_F, class Q, class TR>
-  static __device__ __forceinline__ double residual_pass(const Q& q, const Consts& P, S* F, SD<S>& sd, const TR& tr) {
+  static __device__ __forceinline__ double residual_pass(const Q& q, const Consts& P, S* F, SD<S>& sd, const TR& tr,
+                                                         Basis* basis = nullptr) {
     Rig<double> X[NE];
     double hs[NJ + 1][3];
     double sc[NB][4];
@@ -553,7 +569,7 @@ struct Leaf {
           }
           sfor<0, NB>([&](auto BI) {
             constexpr int b = decltype(BI)::value;
-            if constexpr (last_joint(b) == j) finish_block<b, WITH_F>(X, bc, F, n2, sd, sc);
+            if constexpr (last_joint(b) == j) finish_block<b, WITH_F>(X, bc, F, n2, sd, sc, basis);
           });
         },
         [&](auto G) { load_blocks<decltype(G)::value>(bc, P.d); });
@@ -582,12 +598,66 @@ struct Leaf {
       if constexpr (is_pose(b) || is_rel(b)) {
         for (int k = 0; k < 3; ++k) {
           const double w = fa[b] * sc[b][k];
+          if (basis) basis->w[b][k] = w;
           F[KI::brow0(b) + 3 + k] = to_step<S>(w);
           n2 += w * w;
         }
       }
     });
     return n2;
+  }
+
+  // y' = T^T c (FORWARD) or its inverse c = T^-T y', in place: the rotations R^T and R on the linear rows, the inverse left
+  // Jacobian J_l^-1(w) and J_l(w) on the angular ones (J_l = I + B [w]x + C [w]x^2, J_l^-1 = I - [w]x / 2 + beta [w]x^2).
+  template <bool FORWARD, class TR>
+  static __device__ __forceinline__ void change_rows(const Basis& bs, const TR& tr, double* y) {
+    sfor<0, NB>([&](auto BI) {
+      constexpr int b = decltype(BI)::value, r0 = KI::brow0(b);
+      if constexpr (is_pose(b) || is_rel(b)) {
+        const double* R = bs.R[b];
+        const double* w = bs.w[b];
+        double l[3];
+        for (int k = 0; k < 3; ++k)
+          l[k] = FORWARD ? R[k] * y[r0] + R[3 + k] * y[r0 + 1] + R[6 + k] * y[r0 + 2]
+                         : R[3 * k] * y[r0] + R[3 * k + 1] * y[r0 + 1] + R[3 * k + 2] * y[r0 + 2];
+        for (int k = 0; k < 3; ++k) y[r0 + k] = l[k];
+        const double t2 = w[0] * w[0] + w[1] * w[1] + w[2] * w[2];
+        double B, C;  // of J_l; for the inverse B = -1/2, C = beta
+        if (t2 < 0.1) {  // series to theta^10, remainders below 1e-17
+          if constexpr (FORWARD) {
+            C = 1.0 / 12 + t2 * (1.0 / 720 + t2 * (1.0 / 30240 + t2 * (1.0 / 1209600 + t2 * (1.0 / 47900160 + t2 * (691.0 / 1307674368000.0)))));
+          } else {
+            B = 0.5 - t2 * (1.0 / 24 - t2 * (1.0 / 720 - t2 * (1.0 / 40320 - t2 * (1.0 / 3628800 - t2 / 479001600.0))));
+            C = 1.0 / 6 - t2 * (1.0 / 120 - t2 * (1.0 / 5040 - t2 * (1.0 / 362880 - t2 * (1.0 / 39916800 - t2 / 6227020800.0))));
+          }
+        } else {
+          const double th = sqrt(t2);
+          double sn, cs;
+          sincos_tab(th, tr.tab, sn, cs);
+          if constexpr (FORWARD) {
+            C = 1.0 / t2 - (1.0 + cs) / (2.0 * th * sn);
+          } else {
+            B = (1.0 - cs) / t2;
+            C = (th - sn) / (t2 * th);
+          }
+        }
+        if constexpr (FORWARD) B = -0.5;
+        double* a = y + r0 + 3;
+        double c1[3], c2[3];
+        cross3(w, a, c1);
+        cross3(w, c1, c2);
+        for (int k = 0; k < 3; ++k) a[k] += B * c1[k] + C * c2[k];
+      }
+    });
+  }
+  // Take the base point's choice of rows (dropped rows, polygon row map) into sd: the smooth piece that is active there.
+  static __device__ __forceinline__ void freeze_rows(SD<double>& sd, const SD<double>& base) {
+    sd.drop = base.drop;
+    sfor<0, NB>([&](auto BI) {
+      constexpr int b = decltype(BI)::value;
+      if constexpr (Topo::btype[b] == B_HULL)
+        for (int k = 0; k < 3; ++k) sd.H[b][k] = base.H[b][k];
+    });
   }
 
   // ---------------------------------------------------------------- step passes

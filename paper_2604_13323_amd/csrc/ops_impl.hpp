@@ -118,7 +118,8 @@ hipError_t OpsImpl<Model, IO, S>::vjp(const VjpArgs& a, hipStream_t s) {
 template <class Model, class IO, class S>
 hipError_t OpsImpl<Model, IO, S>::vjp_exact(const VjpxArgs& a, hipStream_t s) {
   // LDS per wave: the FP64 iterate and cotangent tiles and the FP32 direction tile
-  hipLaunchKernelGGL((k_vjp_exact<Model, IO>), dim3(blocks_for(a.n, 64)), dim3(64), size_t(Model::D) * 64 * 20, s, a);
+  hipLaunchKernelGGL((k_vjp_exact<Model, IO>), dim3(blocks_for(a.n, 64)), dim3(64),
+                     8 * size_t(kTabDoubles<Model>) + size_t(Model::D) * 64 * 20, s, a);
   return hipGetLastError();
 }
 template <class Model, class IO, class S>
