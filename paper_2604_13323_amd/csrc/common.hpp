@@ -265,13 +265,15 @@ static __constant__ MathTab kMathTab = {
 // Cody-Waite reduction x = k pi/2 + r with pi/2 split into three doubles (hi + mid + lo),
 // then the Taylor series of sin (to r^15) and cos (to r^16) on |r| <= pi/4, whose
 // truncation errors are below 5e-17. No large-argument path.
-__device__ __forceinline__ void sincos_t(double x, double* s, double* c) {
+// tab: gives the coefficients, once r^2 exists.
+template <class TAB>
+__device__ __forceinline__ void sincos_with(double x, TAB&& tab, double* s, double* c) {
   const double k = __builtin_rint(x * 0.6366197723675814);
   double r = __builtin_fma(-k, 1.5707963267948966, x);
   r = __builtin_fma(-k, 6.123233995736766e-17, r);
   r = __builtin_fma(-k, -1.4973849048591698e-33, r);
   const double r2 = r * r;
-  const MathTab& T = after_const(kMathTab, r2);
+  const MathTab& T = tab(r2);
   double ps = T.sin_c[0];
   for (int i = 1; i < 7; ++i) ps = fma_su(ps, r2, T.sin_c[i]);
   const double sn = __builtin_fma(ps * r2, r, r);
@@ -283,6 +285,9 @@ __device__ __forceinline__ void sincos_t(double x, double* s, double* c) {
   const double c0 = (qd & 1) ? sn : cs;
   *s = (qd & 2) ? -s0 : s0;
   *c = ((qd + 1) & 2) ? -c0 : c0;
+}
+__device__ __forceinline__ void sincos_t(double x, double* s, double* c) {
+  sincos_with(x, [](double r2) -> const MathTab& { return after_const(kMathTab, r2); }, s, c);
 }
 __device__ __forceinline__ void sincos_t(float x, float* s, float* c) { __sincosf(x, s, c); }
 __device__ __forceinline__ double rsqrt_t(double x) { return rsqrt(x); }
@@ -342,6 +347,8 @@ struct QArr {  // registers
   __device__ __forceinline__ double at(int j) const { return double(opaque(q[j])); }
   template <class U>
   __device__ __forceinline__ double at(int j, U dep) const { return double(after(q[j], dep)); }
+  __device__ __forceinline__ double get(int j) const { return double(q[j]); }
+  __device__ __forceinline__ QArr fresh() const { return *this; }
 };
 
 constexpr int pidx(int i, int k) { return i * (i + 1) / 2 + k; }  // packed lower triangle, i >= k

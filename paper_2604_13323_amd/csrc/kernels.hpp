@@ -81,6 +81,7 @@ struct QGlob {  // configuration i of a [D][ld] array in global memory
   template <class U>
   __device__ __forceinline__ double at(int j, U) const { return at(j); }
   __device__ __forceinline__ double get(int j) const { return at(j); }
+  __device__ __forceinline__ QGlob fresh() const { return *this; }
 };
 
 // ------------------------------------------------------------------ Cholesky

@@ -357,9 +357,26 @@ struct Kin {
   static constexpr bool in_rows(uint32_t rm, int r) { return (rm >> r) & 1u; }
   static constexpr bool lnz(int i, int k) { return KI::LP.nz[i][k]; }
 
+  // The single arms: a walk of the chain reads the coordinates and takes their sines and cosines side by side before it
+  // composes the frames, reads a joint's constants while the joint before is computed, and keeps the joints' axes and
+  // origins (42 values) for the passes after it. Longer walks would not hold them in registers. Bound by the latency of
+  // the chain of frames, one or two waves per SIMD: with a walk per pass (FP64 residual, Gram, J^T y), each joint's
+  // coordinate, sine coefficients and constants awaited in turn, the projection of 131,072 arm configurations with a
+  // bounded region (30 steps for 151 of them) took 305 us, so 256 us (and as many full waves as fill the card twice 7.5 us a step, 4 cycles an
+  // instruction).
+  static constexpr bool chain() {
+    bool c = !Topo::has_com && NF == 1 && NB == 1 && NJ >= 2 && Topo::frame_link[0] == NJ - 1;
+    for (int j = 0; j < NJ; ++j) c = c && Topo::parent[j] == j - 1;
+    return c;
+  }
+  static constexpr bool one_walk = NJ <= 8 && chain();
+
   // Per-iteration data from the residual pass used by the Jacobian passes.
   template <class S>
   struct SD {
+    // one_walk: joint axes and origins, from the residual pass (FP64) or the Gram pass (FP32)
+    mutable S ax[one_walk ? NJ : 1][3];
+    mutable S org[one_walk ? NJ : 1][3];
     S pend[NB][3];    // end point of pose / relative-pose blocks
     S W[NB][9];       // REL: (R_a R_ref)^T
     S A[NB][9];       // J_l^-1(w) W
@@ -420,9 +437,10 @@ struct Kin {
     return r;
   }
 
-  // Frame X of joint j from its parent's frame B (not read where the parent is the world).
-  template <class T, int j>
-  static __device__ __forceinline__ void joint_frame(const Rig<T>& B, const JP<T>& cur, Rig<T>& X) {
+  // Frame X of joint j from its parent's frame B (not read where the parent is the world); sc: sine and cosine of a
+  // revolute coordinate.
+  template <class T, int j, class SC>
+  static __device__ __forceinline__ void joint_frame(const Rig<T>& B, const JP<T>& cur, Rig<T>& X, SC&& sc) {
     constexpr int par = Topo::parent[j];
     constexpr int ax = Topo::axis[j];
     if constexpr (par < 0) {
@@ -446,7 +464,7 @@ struct Kin {
       for (int r = 0; r < 3; ++r) X.p[r] += X.R[3 * r + ax] * cur.q;
     } else {
       T s, c;
-      sincos_t(cur.q, &s, &c);
+      sc(s, c);
       constexpr int i = (ax + 1) % 3, k = (ax + 2) % 3;
       for (int r = 0; r < 3; ++r) {
         const T a = X.R[3 * r + i], b = X.R[3 * r + k];
@@ -454,6 +472,11 @@ struct Kin {
         X.R[3 * r + k] = b * c - a * s;
       }
     }
+  }
+
+  template <class T, int j>
+  static __device__ __forceinline__ void joint_frame(const Rig<T>& B, const JP<T>& cur, Rig<T>& X) {
+    joint_frame<T, j>(B, cur, X, [&](T& s, T& c) { sincos_t(cur.q, &s, &c); });
   }
 
   // Forward kinematics, streaming each link frame to visit(ic<j>, frame, joint data) in joint
@@ -481,9 +504,82 @@ struct Kin {
     });
   }
 
+  // The constants of joint j, read while joint j - 1 is computed.
+  template <class T, int j>
+  static __device__ __forceinline__ void chain_joint(const TP<T>& P, JP<T>& r) {
+    for (int k = 0; k < 3; ++k) r.p[k] = P.jp[j][k];
+    if constexpr (Topo::origin_rot)
+      for (int k = 0; k < 9; ++k) r.R[k] = P.jR[j][k];
+  }
+  // fk() of a one_walk chain.
+  template <class T, class Q, class V>
+  static __device__ __forceinline__ void fk_chain(const Q& q, const TP<T>& P, V&& visit) {
+    const MathTab& mt = fresh_const(kMathTab);
+    const Q qf = q.fresh();
+    JP<T> cur, nxt;
+    chain_joint<T, 0>(fresh_const(P), cur);
+    T x[NJ], sn[NJ], cs[NJ];
+    double xd[NJ];
+    for (int j = 0; j < NJ; ++j) xd[j] = qf.get(j);
+    sfor<0, NJ>([&](auto J) {
+      constexpr int j = decltype(J)::value;
+      x[j] = joint_value<T, Topo::jtype[j]>(xd[j]);
+      if constexpr (Topo::jtype[j] == REV) {
+        if constexpr (std::is_same<T, double>::value) sincos_with(x[j], [&](double) -> const MathTab& { return mt; }, &sn[j], &cs[j]);
+        else sincos_t(x[j], &sn[j], &cs[j]);
+      }
+    });
+    Rig<T> L[NJ];
+    sfor<0, NJ>([&](auto J) {
+      constexpr int j = decltype(J)::value;
+      if constexpr (j + 1 < NJ) {
+        __builtin_amdgcn_sched_barrier(0);
+        chain_joint<T, j + 1>(after_const(P, j > 0 ? L[j > 0 ? j - 1 : 0].p[2] : x[0]), nxt);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      cur.q = x[j];
+      joint_frame<T, j>(L[j > 0 ? j - 1 : 0], cur, L[j], [&](T& s, T& c) {
+        s = sn[j];
+        c = cs[j];
+      });
+      visit(J, L[j], cur);
+      cur = nxt;
+    });
+  }
+  // The walk of a step pass: fk(), and for a one_walk chain the pass that makes the axes and origins (FIRST) or those kept.
+  template <class S, bool FIRST, class Q, class V>
+  static __device__ __forceinline__ void walk(const Q& q, const TP<S>& T, const SD<S>& sd, V&& visit) {
+    if constexpr (!one_walk) {
+      fk<S>(q, T, visit);
+    } else if constexpr (FIRST && std::is_same<S, float>::value) {
+      fk_chain<S>(q, T, [&](auto J, const Rig<S>& X, const JP<S>& jp) {
+        keep<S, decltype(J)::value>(X, sd);
+        visit(J, X, jp);
+      });
+    } else {
+      const JP<S> none = {};
+      sfor<0, NJ>([&](auto J) {
+        constexpr int j = decltype(J)::value;
+        Rig<S> X;
+        for (int k = 0; k < 3; ++k) {
+          X.R[3 * k + Topo::axis[j]] = sd.ax[j][k];
+          X.p[k] = sd.org[j][k];
+        }
+        visit(J, X, none);
+      });
+    }
+  }
+  template <class S, int j>
+  static __device__ __forceinline__ void keep(const Rig<S>& X, const SD<S>& sd) {
+    for (int k = 0; k < 3; ++k) {
+      sd.ax[j][k] = X.R[3 * k + Topo::axis[j]];
+      sd.org[j][k] = X.p[k];
+    }
+  }
+
   template <class T>
   static __device__ __forceinline__ void frame_pose(const Rig<T>& X, const TP<T>& P0, int f, Rig<T>& out) {
-    const TP<T>& P = after_cp(P0, X.p[2]);
+    const TP<T>& P = one_walk ? P0 : after_cp(P0, X.p[2]);
     if constexpr (Topo::frame_rot) {
       matmul3(X.R, P.fR[f], out.R);
     } else {
@@ -528,9 +624,9 @@ struct Kin {
   static __device__ __forceinline__ void block_rows(const Rig<double>* Fr, const Consts& P0, S* F, double& n2, SD<S>& sd) {
     constexpr int t = Topo::btype[b];
     constexpr int r0 = KI::brow0(b);
-    // the block's constants are read only once its frames exist
+    // the block's constants are read only once its frames exist (one_walk: by the caller, ahead)
     constexpr int flast = (t == B_REL || t == B_DIST) ? Topo::bfb[b] : Topo::bfa[b];
-    const Consts& P = after_cp(P0, Fr[flast < 0 ? 0 : flast].p[2]);
+    const Consts& P = one_walk ? P0 : after_cp(P0, Fr[flast < 0 ? 0 : flast].p[2]);
     if constexpr (t == B_POSE) {
       constexpr int fa = Topo::bfa[b];
       const double* Rt = P.d.refRt[b];
@@ -650,48 +746,61 @@ struct Kin {
   // entries of F and sd are left untouched.
   template <class S, uint32_t RM = ALL, class Q>
   static __device__ __forceinline__ double residual(const Q& q, const Consts& P, S* F, SD<S>& sd) {
-    Rig<double> Fr[NF];
-    double cm[3] = {0.0, 0.0, 0.0};
-    double n2 = 0.0;
-    fk<double>(q, P.d, [&](auto J, const Rig<double>& X, const JP<double>& jp) {
-      constexpr int j = decltype(J)::value;
-      sfor<0, NF>([&](auto FI) {
-        constexpr int f = decltype(FI)::value;
-        if constexpr (Topo::frame_link[f] == j) frame_pose<double>(X, P.d, f, Fr[f]);
+    if constexpr (one_walk) {
+      Rig<double> L[NJ], Fr[NF];
+      double n2 = 0.0;
+      fk_chain<double>(q, P.d, [&](auto J, const Rig<double>& X, const JP<double>&) {
+        constexpr int j = decltype(J)::value;
+        L[j] = X;
+        if constexpr (std::is_same<S, double>::value) keep<S, j>(X, sd);
       });
-      if constexpr (Topo::has_com) {
-        if constexpr (!Topo::massless(j)) {
-          double t[3];
-          matvec3(X.R, jp.mc, t);
-          // accumulated here, at its joint: the link's mass constants are then dead at once
-          // instead of being kept (spilled) until the CoM rows at the end of the walk
-          for (int k = 0; k < 3; ++k) cm[k] = opaque(cm[k] + t[k] + jp.m * X.p[k]);
+      frame_pose<double>(L[NJ - 1], after_const(P.d, L[NJ - 2].p[2]), 0, Fr[0]);
+      block_rows<S, 0>(Fr, after_const(P, L[NJ - 1].p[2]), F, n2, sd);
+      return n2;
+    } else {
+      Rig<double> Fr[NF];
+      double cm[3] = {0.0, 0.0, 0.0};
+      double n2 = 0.0;
+      fk<double>(q, P.d, [&](auto J, const Rig<double>& X, const JP<double>& jp) {
+        constexpr int j = decltype(J)::value;
+        sfor<0, NF>([&](auto FI) {
+          constexpr int f = decltype(FI)::value;
+          if constexpr (Topo::frame_link[f] == j) frame_pose<double>(X, P.d, f, Fr[f]);
+        });
+        if constexpr (Topo::has_com) {
+          if constexpr (!Topo::massless(j)) {
+            double t[3];
+            matvec3(X.R, jp.mc, t);
+            // accumulated here, at its joint: the link's mass constants are then dead at once
+            // instead of being kept (spilled) until the CoM rows at the end of the walk
+            for (int k = 0; k < 3; ++k) cm[k] = opaque(cm[k] + t[k] + jp.m * X.p[k]);
+          }
+          if constexpr (KI::end_needed(j + 1)) {
+            for (int k = 0; k < 3; ++k) sd.Qe[j + 1][k] = to_step<S>(cm[k]);
+          }
         }
-        if constexpr (KI::end_needed(j + 1)) {
-          for (int k = 0; k < 3; ++k) sd.Qe[j + 1][k] = to_step<S>(cm[k]);
-        }
-      }
+        sfor<0, NB>([&](auto BI) {
+          constexpr int b = decltype(BI)::value;
+          if constexpr (KI::complete_link(b) == j && sel<RM>(b)) block_rows<S, b>(Fr, P, F, n2, sd);
+        });
+      });
       sfor<0, NB>([&](auto BI) {
         constexpr int b = decltype(BI)::value;
-        if constexpr (KI::complete_link(b) == j && sel<RM>(b)) block_rows<S, b>(Fr, P, F, n2, sd);
+        if constexpr (Topo::btype[b] == B_COM && sel<RM>(b)) {
+          constexpr int r0 = KI::brow0(b);
+          const TP<double>& Pd = after_cp(P.d, cm[1]);
+          const double e0 = cm[0] * Pd.inv_total_mass - Pd.target[b][0];
+          const double e1 = cm[1] * Pd.inv_total_mass - Pd.target[b][1];
+          F[r0] = to_step<S>(e0);
+          F[r0 + 1] = to_step<S>(e1);
+          n2 += e0 * e0 + e1 * e1;
+        } else if constexpr (Topo::btype[b] == B_HULL && sel<RM>(b)) {
+          const TP<double>& Pd = after_cp(P.d, cm[1]);
+          hull_rows<S, b>(cm[0] * Pd.inv_total_mass, cm[1] * Pd.inv_total_mass, P, F, n2, sd);
+        }
       });
-    });
-    sfor<0, NB>([&](auto BI) {
-      constexpr int b = decltype(BI)::value;
-      if constexpr (Topo::btype[b] == B_COM && sel<RM>(b)) {
-        constexpr int r0 = KI::brow0(b);
-        const TP<double>& Pd = after_cp(P.d, cm[1]);
-        const double e0 = cm[0] * Pd.inv_total_mass - Pd.target[b][0];
-        const double e1 = cm[1] * Pd.inv_total_mass - Pd.target[b][1];
-        F[r0] = to_step<S>(e0);
-        F[r0 + 1] = to_step<S>(e1);
-        n2 += e0 * e0 + e1 * e1;
-      } else if constexpr (Topo::btype[b] == B_HULL && sel<RM>(b)) {
-        const TP<double>& Pd = after_cp(P.d, cm[1]);
-        hull_rows<S, b>(cm[0] * Pd.inv_total_mass, cm[1] * Pd.inv_total_mass, P, F, n2, sd);
-      }
-    });
-    return n2;
+      return n2;
+    }
   }
 
   // Structurally nonzero entries of Jacobian column j (other rows untouched). Qr is the running
@@ -789,7 +898,7 @@ struct Kin {
       }
     });
     S Qr[3] = {S(0), S(0), S(0)};
-    fk<S>(q, T, [&](auto J, const Rig<S>& X, const JP<S>& jp) {
+    walk<S, true>(q, T, sd, [&](auto J, const Rig<S>& X, const JP<S>& jp) {
       constexpr int j = decltype(J)::value;
       S col[M];
       column<S, j, RM>(X, jp, T, sd, Qr, col);
@@ -813,7 +922,7 @@ struct Kin {
     const TP<S>& T = tp<S>(P);
     for (int i = 0; i < M; ++i) v[i] = S(0);
     S Qr[3] = {S(0), S(0), S(0)};
-    fk<S>(q, T, [&](auto J, const Rig<S>& X, const JP<S>& jp) {
+    walk<S, false>(q, T, sd, [&](auto J, const Rig<S>& X, const JP<S>& jp) {
       constexpr int j = decltype(J)::value;
       S col[M];
       column<S, j>(X, jp, T, sd, Qr, col);
@@ -831,7 +940,7 @@ struct Kin {
   static __device__ __forceinline__ void jty(const Q& q, const Consts& P, const SD<S>& sd, const S* y, OUT&& out) {
     const TP<S>& T = tp<S>(P);
     S Qr[3] = {S(0), S(0), S(0)};
-    fk<S>(q, T, [&](auto J, const Rig<S>& X, const JP<S>& jp) {
+    walk<S, false>(q, T, sd, [&](auto J, const Rig<S>& X, const JP<S>& jp) {
       constexpr int j = decltype(J)::value;
       S col[M];
       column<S, j, RM>(X, jp, T, sd, Qr, col);
@@ -850,7 +959,7 @@ struct Kin {
     const TP<S>& T = tp<S>(P);
     S Qr[3] = {S(0), S(0), S(0)};
     for (int k = 0; k < M * D; ++k) Jd[k] = S(0);
-    fk<S>(q, T, [&](auto J, const Rig<S>& X, const JP<S>& jp) {
+    walk<S, true>(q, T, sd, [&](auto J, const Rig<S>& X, const JP<S>& jp) {
       constexpr int j = decltype(J)::value;
       S col[M];
       column<S, j>(X, jp, T, sd, Qr, col);
