@@ -628,8 +628,10 @@ constexpr int kExtNone = 127;  // no failure recorded at this level
 // particles p_i = q_steer + eps_i v (one thread per particle, particle i of extension e at i E + e)
 template <class T>
 __global__ void __launch_bounds__(256) k_ext_particles(int64_t E, int n, int d, const T* qs, const T* qt, int64_t ld, const T* eps, double r,
-                                T* part, int64_t ldp, double* dist, int8_t* result, int32_t* particle, int32_t* npts) {
+                                T* part, int64_t ldp, double* dist, int8_t* result, int32_t* particle, int32_t* npts,
+                                unsigned int* count) {
   const int64_t g = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+  if (g == 0) *count = 0u;  // slots of level 0
   if (g >= E * n) return;
   const int64_t i = g / E, e = g - i * E;
   double a[kMaxD], v[kMaxD];
@@ -659,13 +661,32 @@ __global__ void __launch_bounds__(256) k_ext_particles(int64_t E, int n, int d, 
   }
 }
 
-// earliest converged particle, its collision verdict and distance test; seeds the chain ends
+// Gives each extension that goes on (alive) a slot of the level's batch (wave-aggregated atomic) and clears its record of
+// the level. Called by whole waves.
+__device__ __forceinline__ void ext_slot(bool alive, int64_t e, int32_t* code, unsigned long long* maxgap, int32_t* slot_ext,
+                                         unsigned int* count) {
+  if (alive) {
+    code[e] = kExtNone;
+    maxgap[e] = 0ull;
+  }
+  const uint64_t m = uint64_t(__ballot(alive));
+  if (m == 0) return;
+  const int lane = int(threadIdx.x & 63);
+  const int leader = __builtin_ctzll(m);
+  unsigned int base = 0;
+  if (lane == leader) base = atomicAdd(count, (unsigned int)__builtin_popcountll(m));
+  base = __shfl(base, leader);
+  if (alive) slot_ext[base + __builtin_popcountll(m & ((1ull << lane) - 1ull))] = int32_t(e);
+}
+
+// earliest converged particle of extension e, its collision verdict and distance test; seeds the chain ends. Returns
+// whether the extension goes on.
 template <class T>
-__global__ void __launch_bounds__(256) k_ext_select(int64_t E, int n, int d, const T* qs, int64_t ld, const T* pout, int64_t ldp,
-                             const int8_t* st, const int8_t* it, const uint8_t* vd, const double* dist, int8_t* result,
-                             int32_t* particle, T* q_out, int64_t ld_out, T* chain, int64_t K, int64_t H) {
-  const int64_t e = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (e >= E || result[e] != kExtRunning) return;
+__device__ __forceinline__ bool ext_select(int64_t e, int64_t E, int n, int d, const T* qs, int64_t ld, const T* pout, int64_t ldp,
+                                           const int8_t* st, const int8_t* it, const uint8_t* vd, const double* dist,
+                                           int8_t* result, int32_t* particle, T* q_out, int64_t ld_out, T* chain, int64_t K,
+                                           int64_t H) {
+  if (e >= E || result[e] != kExtRunning) return false;
   int best = -1, best_it = 1 << 30;
   for (int i = 0; i < n; ++i) {
     const int64_t g = int64_t(i) * E + e;
@@ -676,7 +697,7 @@ __global__ void __launch_bounds__(256) k_ext_select(int64_t E, int n, int d, con
   }
   if (best < 0) {
     result[e] = MC_EXT_NO_PARTICLE;
-    return;
+    return false;
   }
   particle[e] = best;
   const int64_t g = int64_t(best) * E + e;
@@ -698,44 +719,39 @@ __global__ void __launch_bounds__(256) k_ext_select(int64_t E, int n, int d, con
     const double t = double(qb[c]) - double(qa[c]);
     s2 += t * t;
   }
+  const bool far = sqrt(s2) > 2.0 * dist[e];
   if (vd[g] != V_FREE) result[e] = MC_EXT_COLLISION;
-  else if (sqrt(s2) > 2.0 * dist[e]) result[e] = MC_EXT_TOO_FAR;
+  else if (far) result[e] = MC_EXT_TOO_FAR;
+  return vd[g] == V_FREE && !far;
+}
+// one thread per extension, with the bookkeeping of level 0
+template <class T>
+__global__ void __launch_bounds__(256) k_ext_select(int64_t E, int n, int d, const T* qs, int64_t ld, const T* pout, int64_t ldp,
+                             const int8_t* st, const int8_t* it, const uint8_t* vd, const double* dist, int8_t* result,
+                             int32_t* particle, T* q_out, int64_t ld_out, T* chain, int64_t K, int64_t H, int32_t* code,
+                             unsigned long long* maxgap, int32_t* slot_ext, unsigned int* count) {
+  const int64_t e = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+  const bool alive = ext_select(e, E, n, d, qs, ld, pout, ldp, st, it, vd, dist, result, particle, q_out, ld_out, chain, K, H);
+  ext_slot(alive, e, code, maxgap, slot_ext, count);
 }
 
-// Level bookkeeping, one thread per extension: applies the previous level's failure code, ends
-// extensions whose chain meets the resolution, and gives each extension that goes on a slot of
-// the level's batch (wave-aggregated atomic).
+// Level bookkeeping after a level (level > 0), one thread per extension: applies the previous level's failure code, ends
+// extensions whose chain meets the resolution, and gives the others their slots.
 __global__ void __launch_bounds__(256) k_ext_level(int64_t E, int n, int level, int lmax, double delta, int8_t* result, int32_t* npts,
                             int32_t* code, unsigned long long* maxgap, int32_t* slot_ext, unsigned int* count) {
   const int64_t e = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
   bool alive = false;
   if (e < E && result[e] == kExtRunning) {
-    if (level > 0) {
-      if (code[e] != kExtNone) {
-        result[e] = int8_t(code[e]);
-      } else if (__longlong_as_double((long long)maxgap[e]) <= delta || level > lmax) {
-        result[e] = MC_EXT_OK;
-        npts[e] = int32_t((int64_t(n) + 1) << (level - 1)) + 1;
-      } else {
-        alive = true;
-      }
+    if (code[e] != kExtNone) {
+      result[e] = int8_t(code[e]);
+    } else if (__longlong_as_double((long long)maxgap[e]) <= delta || level > lmax) {
+      result[e] = MC_EXT_OK;
+      npts[e] = int32_t((int64_t(n) + 1) << (level - 1)) + 1;
     } else {
       alive = true;
     }
-    if (level > lmax) alive = false;
-    if (alive) {
-      code[e] = kExtNone;
-      maxgap[e] = 0ull;
-    }
   }
-  const uint64_t m = uint64_t(__ballot(alive));
-  if (m == 0) return;
-  const int lane = int(threadIdx.x & 63);
-  const int leader = __builtin_ctzll(m);
-  unsigned int base = 0;
-  if (lane == leader) base = atomicAdd(count, (unsigned int)__builtin_popcountll(m));
-  base = __shfl(base, leader);
-  if (alive) slot_ext[base + __builtin_popcountll(m & ((1ull << lane) - 1ull))] = int32_t(e);
+  ext_slot(alive, e, code, maxgap, slot_ext, count);
 }
 
 // Point g of a level's batch: new point j of the extension in slot s, numbered g = j alive + s
@@ -765,8 +781,9 @@ __device__ __forceinline__ ExtPoint ext_point(int64_t g, int64_t alive, int leve
 // midpoint of every gap
 template <class T>
 __global__ void __launch_bounds__(256) k_ext_emit(int64_t total, int64_t alive, int n, int d, int level, int64_t E, const T* chain,
-                           int64_t K, int64_t H, const int32_t* slot_ext, T* pts, int64_t ldx) {
+                           int64_t K, int64_t H, const int32_t* slot_ext, T* pts, int64_t ldx, unsigned int* count) {
   const int64_t g = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+  if (g == 0) *count = 0u;  // slots of the next level (this level's count is read: alive)
   if (g >= total) return;
   const ExtPoint p = ext_point(g, alive, level, H, slot_ext);
   const T* c = chain + p.e;
@@ -787,42 +804,35 @@ __global__ void __launch_bounds__(256) k_ext_emit(int64_t total, int64_t alive, 
   }
 }
 
-// projected points into the chain, with their convergence and collision failures
+// Projected points into the chain, with their convergence and collision failures, and the two gaps next to each new
+// point against the level's bound r / (n 2^level); the longest gap of each extension (non-negative doubles order like
+// their bit patterns). At level 0 a point's neighbours are the points next to it in this batch (the first's and the last's
+// one of the chain's ends), later the two ends of the gap that it halves.
 template <class T>
 __global__ void __launch_bounds__(256) k_ext_store(int64_t total, int64_t alive, int d, int level, int64_t E, T* chain, int64_t K,
                             int64_t H, const int32_t* slot_ext, const T* pout, int64_t ldx, const int8_t* st,
-                            const uint8_t* vd, int32_t* code) {
+                            const uint8_t* vd, double bound, int32_t* code, unsigned long long* maxgap) {
   const int64_t g = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
   if (g >= total) return;
   const ExtPoint p = ext_point(g, alive, level, H, slot_ext);
+  T* c = chain + p.e;
   const int64_t cs = E * K;
-  T x[kMaxD];
-#pragma unroll
-  for (int k = 0; k < kMaxD; ++k) x[k] = k < d ? pout[k * ldx + g] : T(0);
-#pragma unroll
-  for (int k = 0; k < kMaxD; ++k)
-    if (k < d) chain[k * cs + p.pos * E + p.e] = x[k];
-  if (st[g] != ST_CONVERGED) atomicMin(code + p.e, int32_t(MC_EXT_INTERP_FAILED));
-  else if (vd[g] != V_FREE) atomicMin(code + p.e, int32_t(MC_EXT_INTERP_COLLISION));
-}
-
-// the two gaps next to each new point against the level's bound r / (n 2^level); the longest
-// gap of each extension (non-negative doubles order like their bit patterns)
-template <class T>
-__global__ void __launch_bounds__(256) k_ext_gaps(int64_t total, int64_t alive, int d, int level, int64_t E, const T* chain, int64_t K,
-                           int64_t H, const int32_t* slot_ext, double bound, int32_t* code, unsigned long long* maxgap) {
-  const int64_t g = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (g >= total) return;
-  const ExtPoint p = ext_point(g, alive, level, H, slot_ext);
-  const T* c = chain + p.e;
-  const int64_t cs = E * K;
+  const bool prev = level == 0 && p.j > 0, next = level == 0 && g + alive < total;
+  const T* pl = prev ? pout + g - alive : c + p.lo * E;
+  const T* ph = next ? pout + g + alive : c + p.hi * E;
+  const int64_t sl = prev ? ldx : cs, sh = next ? ldx : cs;
   T x[kMaxD], xl[kMaxD], xh[kMaxD];
 #pragma unroll
   for (int k = 0; k < kMaxD; ++k) {
-    x[k] = k < d ? c[k * cs + p.pos * E] : T(0);
-    xl[k] = k < d ? c[k * cs + p.lo * E] : T(0);
-    xh[k] = k < d ? c[k * cs + p.hi * E] : T(0);
+    x[k] = k < d ? pout[k * ldx + g] : T(0);
+    xl[k] = k < d ? pl[k * sl] : T(0);
+    xh[k] = k < d ? ph[k * sh] : T(0);
   }
+#pragma unroll
+  for (int k = 0; k < kMaxD; ++k)
+    if (k < d) c[k * cs + p.pos * E] = x[k];
+  if (st[g] != ST_CONVERGED) atomicMin(code + p.e, int32_t(MC_EXT_INTERP_FAILED));
+  else if (vd[g] != V_FREE) atomicMin(code + p.e, int32_t(MC_EXT_INTERP_COLLISION));
   double a2 = 0.0, b2 = 0.0;
 #pragma unroll
   for (int k = 0; k < kMaxD; ++k) {
@@ -837,6 +847,8 @@ __global__ void __launch_bounds__(256) k_ext_gaps(int64_t total, int64_t alive, 
 
 }  // namespace
 
+constexpr int kCounterStride = 16, kCounterWords = 10 * kCounterStride;
+
 struct mc_problem {
   int family = 0, d = 0, m = 0, device = 0, n_cu = 0;
   size_t max_lds_per_block = 0;
@@ -844,8 +856,13 @@ struct mc_problem {
   float4* obs = nullptr;
   float4* obs_pad = nullptr;
   int n_obs = 0, n_sph = 0;
-  unsigned int* counter = nullptr;  // [0] work-queue head, [1] projection FP64 queue, [2] VJP FP64 queue,
-                                    // [3] exact-check queue
+  // Queue counters: for the projection, the VJP and the check three sets each (kCounterStride words apart, kCounters of
+  // them used) and a set that stays zero (take_counters). A set of the projection: [0] work-queue head, [1] FP64 queue,
+  // [3] exact-check queue; of the VJP and the check: [0] their queue.
+  unsigned int* counter = nullptr;
+  mutable int counter_set[3] = {0, 0, 0};         // the set the last call used, 0 or 1
+  mutable bool counter_clean[3] = {true, true, true};  // the other one is zero, or will be before a later call on the stream
+  mutable const unsigned int* counts[4] = {};     // the last call's counters, as mc_queue_counts reports them
   unsigned long long* fallback = nullptr;
   // FP64 tail queues (FP32 mode), grown to the largest batch seen; calls on one handle must not
   // overlap (one stream at a time).
@@ -893,6 +910,37 @@ static hipError_t grow_defer(const mc_problem* p, int64_t n, int dmax) {
   p->defer_cap = n;
   return hipSuccess;
 }
+// The zeroed counters of a call of one kind (0: projection, 1: VJP, 2: check). Two sets take turns: the main kernel of the
+// call that uses one zeroes the other (clear), which the call before it on the handle used, so no launch clears counters
+// (a launch of one small kernel before the main one took 4.7 us of a call). Under stream capture the third set, zeroed by a
+// kernel of the graph: replays do not take turns with other calls. The caller reports its main kernel's launch: a
+// failed one leaves the other set as it was.
+enum : int { kProjectCounters = 0, kVjpCounters = 1, kCheckCounters = 2 };
+static hipError_t take_counters(const mc_problem* p, int kind, hipStream_t s, unsigned int** use, unsigned int** clear) {
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &cs) != hipSuccess) {  // the default stream, while another one captures
+    (void)hipGetLastError();
+    cs = hipStreamCaptureStatusActive;
+  }
+  unsigned int* base = p->counter + 3 * kind * kCounterStride;
+  *clear = nullptr;
+  if (cs != hipStreamCaptureStatusNone) {
+    *use = base + 2 * kCounterStride;
+    hipLaunchKernelGGL(k_reset_u32, dim3(1), dim3(64), 0, s, *use, kCounters);
+    return hipGetLastError();
+  }
+  if (!p->counter_clean[kind]) {
+    hipLaunchKernelGGL(k_reset_u32, dim3(1), dim3(64), 0, s, base, 2 * kCounterStride);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  p->counter_clean[kind] = false;
+  const int set = p->counter_set[kind] ^= 1;
+  *use = base + set * kCounterStride;
+  *clear = base + (set ^ 1) * kCounterStride;
+  return hipSuccess;
+}
+
 static hipError_t grow_vjp(const mc_problem* p, int64_t n) {
   if (n <= p->vjp_cap) return hipSuccess;
   hipError_t e;
@@ -1120,7 +1168,7 @@ mc_status mc_problem_create(const void* blob, size_t nbytes, mc_problem** out) {
   if ((e = alloc((void**)&p->dev, sizeof(DevProblem))) != hipSuccess ||
       (e = alloc((void**)&p->obs, obs_f.size() * sizeof(float4))) != hipSuccess ||
       (e = alloc((void**)&p->obs_pad, pad_f.size() * sizeof(float4))) != hipSuccess ||
-      (e = alloc((void**)&p->counter, 4 * sizeof(unsigned int))) != hipSuccess ||
+      (e = alloc((void**)&p->counter, kCounterWords * sizeof(unsigned int))) != hipSuccess ||
       (e = alloc((void**)&p->fallback, sizeof(unsigned long long))) != hipSuccess) {
     mc_problem_destroy(p);
     delete hp;
@@ -1129,14 +1177,15 @@ mc_status mc_problem_create(const void* blob, size_t nbytes, mc_problem** out) {
   hp->obs = p->obs;
   hp->obs_pad = p->obs_pad;
   hp->fallback_counter = p->fallback;
+  for (const unsigned int*& c : p->counts) c = p->counter + 9 * kCounterStride;
   p->n_obs = K.n_obs;
   p->n_sph = K.n_sph;
   const unsigned long long zero64 = 0;
-  const unsigned int zero32[4] = {0, 0, 0, 0};
+  const std::vector<unsigned int> zero32(kCounterWords, 0u);
   if ((e = hipMemcpy(p->dev, hp, sizeof(DevProblem), hipMemcpyHostToDevice)) != hipSuccess ||
       (!obs_f.empty() && (e = hipMemcpy(p->obs, obs_f.data(), obs_f.size() * sizeof(float4), hipMemcpyHostToDevice)) != hipSuccess) ||
       (!pad_f.empty() && (e = hipMemcpy(p->obs_pad, pad_f.data(), pad_f.size() * sizeof(float4), hipMemcpyHostToDevice)) != hipSuccess) ||
-      (e = hipMemcpy(p->counter, zero32, sizeof zero32, hipMemcpyHostToDevice)) != hipSuccess ||
+      (e = hipMemcpy(p->counter, zero32.data(), zero32.size() * sizeof(unsigned int), hipMemcpyHostToDevice)) != hipSuccess ||
       (e = hipMemcpy(p->fallback, &zero64, sizeof zero64, hipMemcpyHostToDevice)) != hipSuccess) {
     mc_problem_destroy(p);
     delete hp;
@@ -1250,7 +1299,7 @@ static mc_status project_impl(const mc_problem* p, int64_t n, const void* q_in, 
     mc_status sst = scratch_on_current_device(&scr);
     if (sst != MC_OK) return sst;
   }
-  unsigned int* counter = noalloc ? reinterpret_cast<unsigned int*>(scr) : p->counter;
+  unsigned int* counter = nullptr;
 
   ProjArgs a;
   std::memset(&a, 0, sizeof a);
@@ -1270,7 +1319,6 @@ static mc_status project_impl(const mc_problem* p, int64_t n, const void* q_in, 
   a.max_iter = opts->max_iter;
   a.check = opts->check_collision;
   a.outer = opts->step_form;
-  a.counter = counter;
   a.n_sph = p->n_sph;
   a.n_obs = p->n_obs;
   a.chk_lanes = p->check_lanes;
@@ -1314,6 +1362,20 @@ static mc_status project_impl(const mc_problem* p, int64_t n, const void* q_in, 
     a.n_static = std::min<int64_t>(n, grid * block);
     const bool tail = ops->project_tail != nullptr;
     const bool ctail = verdict && opts->check_collision && ops->check_tail != nullptr;
+    if (noalloc) {
+      // counters cleared by a kernel (graph-capturable), never by a memset
+      counter = reinterpret_cast<unsigned int*>(scr);
+      hipLaunchKernelGGL(k_reset_u32, dim3(1), dim3(64), 0, s, counter, kCounters);
+      e = hipGetLastError();
+    } else {
+      if ((tail || ctail) && (e = grow_defer(p, n, ops->dof_max)) != hipSuccess) return hip_fail(e, "project_batch: queue allocation");
+      e = take_counters(p, kProjectCounters, s, &counter, &a.clear);
+      const unsigned int* zero = p->counter + 9 * kCounterStride;
+      const unsigned int* now[4] = {counter, counter + 1, zero, counter + 3};
+      std::copy(now, now + 4, p->counts);
+    }
+    if (e != hipSuccess) return hip_fail(e, "project_batch: reset");
+    a.counter = counter;
     if (tail || ctail) {
       a.defer_count = counter + 1;
       a.chk_count = counter + 3;
@@ -1329,7 +1391,6 @@ static mc_status project_impl(const mc_problem* p, int64_t n, const void* q_in, 
         a.chk_idx = reinterpret_cast<int32_t*>(scr + off);
         a.defer_cap = n;
       } else {
-        if ((e = grow_defer(p, n, ops->dof_max)) != hipSuccess) return hip_fail(e, "project_batch: queue allocation");
         a.defer_ik = p->defer_ik;
         a.defer_q = p->defer_q;
         a.defer_cap = p->defer_cap;
@@ -1338,12 +1399,10 @@ static mc_status project_impl(const mc_problem* p, int64_t n, const void* q_in, 
       }
     }
     a.verdict = verdict;
-    // counters cleared by a kernel (graph-capturable), never by a memset
-    hipLaunchKernelGGL(k_reset_u32, dim3(1), dim3(64), 0, s, counter, 4);
-    if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "project_batch: reset");
     if (p->timing && (e = hipEventRecord(p->tev[0], s)) != hipSuccess) return hip_fail(e, "project_batch: timing event");
     e = (cyc ? ops->project_persistent_cyclic : ops->project_persistent)(a, int(grid), block, s);
     if (e != hipSuccess) return hip_fail(e, "project_batch: persistent launch");
+    if (a.clear) p->counter_clean[kProjectCounters] = true;
     if (p->timing) {
       if ((e = hipEventRecord(p->tev[1], s)) != hipSuccess) return hip_fail(e, "project_batch: timing event");
       p->timed[0] = true;
@@ -1414,7 +1473,6 @@ mc_status check_batch(const mc_problem* p, int64_t n, const void* q, int64_t ld,
   std::memset(&a, 0, sizeof a);
   a.P = p->dev;
   a.verdict = verdict;
-  a.chk_count = p->counter + 3;
   a.chk_idx = p->chk_idx;
   a.chk_q = p->chk_q;
   a.defer_cap = p->defer_cap;
@@ -1422,10 +1480,12 @@ mc_status check_batch(const mc_problem* p, int64_t n, const void* q, int64_t ld,
   a.n_obs = p->n_obs;
   a.chk_lanes = p->check_lanes;
   a.chk_long = p->check_long;
-  hipLaunchKernelGGL(k_reset_u32, dim3(1), dim3(64), 0, s, p->counter + 3, 1);
-  if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "check_batch: reset");
-  if ((e = ops->check_broad(c, a.chk_count, a.chk_idx, a.chk_q, a.defer_cap, s)) != hipSuccess)
+  unsigned int* clear = nullptr;
+  if ((e = take_counters(p, kCheckCounters, s, &a.chk_count, &clear)) != hipSuccess) return hip_fail(e, "check_batch: reset");
+  p->counts[3] = a.chk_count;
+  if ((e = ops->check_broad(c, a.chk_count, a.chk_idx, a.chk_q, a.defer_cap, clear, s)) != hipSuccess)
     return hip_fail(e, "check_batch: broad-phase launch");
+  if (clear) p->counter_clean[kCheckCounters] = true;
   if ((e = ops->check_tail(a, kCheckTailBlocksPerCu * p->n_cu, s)) != hipSuccess) return hip_fail(e, "check_batch: exact-check launch");
   return MC_OK;
 }
@@ -1452,18 +1512,19 @@ mc_status project_vjp(const mc_problem* p, int64_t n, const void* q_proj, int64_
   a.cond_thr = opts->fp64_cond_threshold;
   a.defer_count = nullptr;
   a.defer_idx = nullptr;
+  a.clear = nullptr;
   hipStream_t s = static_cast<hipStream_t>(stream);
   hipError_t e;
   const bool tail = ops->vjp_tail != nullptr;
   if (tail) {
     if ((e = grow_vjp(p, n)) != hipSuccess) return hip_fail(e, "project_vjp: FP64 queue allocation");
-    a.defer_count = p->counter + 2;
+    if ((e = take_counters(p, kVjpCounters, s, &a.defer_count, &a.clear)) != hipSuccess) return hip_fail(e, "project_vjp: reset");
+    p->counts[2] = a.defer_count;
     a.defer_idx = p->vjp_idx;
-    hipLaunchKernelGGL(k_reset_u32, dim3(1), dim3(64), 0, s, p->counter + 2, 1);
-    if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "project_vjp: reset");
   }
   if (p->timing && (e = hipEventRecord(p->tev[2], s)) != hipSuccess) return hip_fail(e, "project_vjp: timing event");
   if ((e = ops->vjp(a, s)) != hipSuccess) return hip_fail(e, "project_vjp: launch");
+  if (a.clear) p->counter_clean[kVjpCounters] = true;
   if (p->timing) {
     if ((e = hipEventRecord(p->tev[3], s)) != hipSuccess) return hip_fail(e, "project_vjp: timing event");
     p->timed[1] = true;
@@ -1645,18 +1706,19 @@ static mc_status extend_impl(const mc_problem* p, int64_t E, const T* qs, const 
   o.variant = 2;
   const int64_t np = E * n;
   hipLaunchKernelGGL(k_ext_particles<T>, dim3((np + 255) / 256), dim3(256), 0, s, E, n, d, qs, qt, ld, eps, xo->r,
-                     pin, EK, w.dist, result, particle, npts);
+                     pin, EK, w.dist, result, particle, npts, w.count);
   if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "extend_batch: particles");
   mc_status st = project_batch(p, np, pin, EK, pout, EK, w.st, w.it, w.rs, w.vd, nullptr, nullptr, 0, nullptr, &o, s);
   if (st != MC_OK) return st;
   hipLaunchKernelGGL(k_ext_select<T>, dim3((E + 255) / 256), dim3(256), 0, s, E, n, d, qs, ld, pout, EK, w.st, w.it,
-                     w.vd, w.dist, result, particle, q_out, ld_out, chain, K, H);
+                     w.vd, w.dist, result, particle, q_out, ld_out, chain, K, H, w.code, w.maxgap, w.slot_ext, w.count);
   if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "extend_batch: select");
   for (int level = 0; level <= lmax + 1; ++level) {
-    hipLaunchKernelGGL(k_reset_u32, dim3(1), dim3(64), 0, s, w.count, 1);
-    hipLaunchKernelGGL(k_ext_level, dim3((E + 255) / 256), dim3(256), 0, s, E, n, level, lmax, xo->delta, result, npts,
-                       w.code, w.maxgap, w.slot_ext, w.count);
-    if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "extend_batch: level");
+    if (level > 0) {
+      hipLaunchKernelGGL(k_ext_level, dim3((E + 255) / 256), dim3(256), 0, s, E, n, level, lmax, xo->delta, result, npts,
+                         w.code, w.maxgap, w.slot_ext, w.count);
+      if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "extend_batch: level");
+    }
     if (level > lmax) break;
     unsigned int alive = 0;
     if ((e = hipMemcpyAsync(&alive, w.count, sizeof alive, hipMemcpyDeviceToHost, s)) != hipSuccess ||
@@ -1667,15 +1729,13 @@ static mc_status extend_impl(const mc_problem* p, int64_t E, const T* qs, const 
     const int64_t total = int64_t(alive) * per;
     const dim3 g((total + 255) / 256), b(256);
     hipLaunchKernelGGL(k_ext_emit<T>, g, b, 0, s, total, int64_t(alive), n, d, level, E, chain, K, H, w.slot_ext,
-                       pin, EK);
+                       pin, EK, w.count);
     if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "extend_batch: emit");
     st = project_batch(p, total, pin, EK, pout, EK, w.st, w.it, w.rs, w.vd, nullptr, nullptr, 0, nullptr, &o, s);
     if (st != MC_OK) return st;
-    hipLaunchKernelGGL(k_ext_store<T>, g, b, 0, s, total, int64_t(alive), d, level, E, chain, K, H, w.slot_ext, pout,
-                       EK, w.st, w.vd, w.code);
     const double bound = xo->r / (double(n) * double(int64_t(1) << level));
-    hipLaunchKernelGGL(k_ext_gaps<T>, g, b, 0, s, total, int64_t(alive), d, level, E, chain, K, H, w.slot_ext, bound,
-                       w.code, w.maxgap);
+    hipLaunchKernelGGL(k_ext_store<T>, g, b, 0, s, total, int64_t(alive), d, level, E, chain, K, H, w.slot_ext, pout,
+                       EK, w.st, w.vd, bound, w.code, w.maxgap);
     if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "extend_batch: validate");
   }
   return MC_OK;
@@ -1774,8 +1834,9 @@ mc_status mc_queue_counts(const mc_problem* p, uint32_t counts[4]) {
   if (!p || !counts) return fail(MC_ERR_INVALID_ARG, "mc_queue_counts: null argument");
   hipError_t e = hipDeviceSynchronize();
   if (e != hipSuccess) return hip_fail(e, "mc_queue_counts: sync");
-  if ((e = hipMemcpy(counts, p->counter, 4 * sizeof(uint32_t), hipMemcpyDeviceToHost)) != hipSuccess)
-    return hip_fail(e, "mc_queue_counts: read");
+  for (int i = 0; i < 4; ++i)
+    if ((e = hipMemcpy(counts + i, p->counts[i], sizeof(uint32_t), hipMemcpyDeviceToHost)) != hipSuccess)
+      return hip_fail(e, "mc_queue_counts: read");
   return MC_OK;
 }
 
@@ -1891,7 +1952,7 @@ mc_status mc_autotune_project(mc_problem* p, int64_t n, const void* q_in, int64_
   mc_launch_shape chosen = kTuneCandidates[best_c >= 0 ? best_c : 0];
   unsigned queued = 0;
   if (rc == MC_OK && opts->check_collision &&
-      (e = hipMemcpy(&queued, p->counter + 3, sizeof queued, hipMemcpyDeviceToHost)) != hipSuccess)
+      (e = hipMemcpy(&queued, p->counts[3], sizeof queued, hipMemcpyDeviceToHost)) != hipSuccess)
     rc = hip_fail(e, "mc_autotune_project: read the check queue length");
   if (rc == MC_OK && opts->check_collision && int64_t(queued) > int64_t(4) * kCheckTailBlocksPerCu * p->n_cu) {
     const int32_t saved = p->check_long;

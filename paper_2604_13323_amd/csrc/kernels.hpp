@@ -44,7 +44,8 @@ struct ProjArgs {
   int32_t max_iter;
   int32_t check;
   int32_t outer;          // 1: the outer form of the step, (J^T J + lambda I)^-1 J^T F (families with D <= kOuterMaxD)
-  unsigned int* counter;  // persistent: queue head (reset to 0 before the launch)
+  unsigned int* counter;  // persistent: queue head (0 at the launch)
+  unsigned int* clear;    // persistent: the counters of the next call, zeroed here (nullptr: none)
   int64_t n_static;       // persistent: configurations [0, n_static) are taken by thread id
   // FP32 mode: configurations whose FP32 step fails (factorisation or condition estimate) are
   // handed to the FP64 tail kernel through this queue: defer_ik[2s], defer_ik[2s+1] = index and
@@ -66,6 +67,7 @@ struct ProjArgs {
 };
 
 constexpr int ST_DEFER = -2;  // internal: continue this configuration with FP64 steps
+constexpr int kCounters = 4;   // queue counters of a call
 
 template <class IO>
 __device__ __forceinline__ double ld_io(const void* p, int64_t k) { return double(static_cast<const IO*>(p)[k]); }
@@ -537,6 +539,7 @@ __device__ __forceinline__ void persistent_body(double* smem) {
   const auto tr = make_trig<Model, TILE>(smem, tiles + Model::D * blockDim.x);
   int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
   const int64_t n = a0.n;
+  if (i < kCounters && a0.clear) a0.clear[i] = 0u;
   if (i >= a0.n_static) i = n;  // not part of the static share
   int k = 0;
   if (i < n) load_q<Model, IO>(a0, dof, i, q);
@@ -818,9 +821,10 @@ __global__ void __launch_bounds__(256) k_check(CheckArgs a) {
 // FP64 configuration) for k_check_tail, which overwrites the verdict of those it finds colliding.
 template <class Model, class IO>
 __global__ void __launch_bounds__(256) k_check_broad(CheckArgs a, unsigned* count, int32_t* idx, double* qbuf,
-                                                     int64_t cap) {
+                                                     int64_t cap, unsigned* clear) {
   const Consts& C = consts_of(a.P);
   const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+  if (i == 0 && clear) *clear = 0u;  // the count of the next call
   if (i >= a.n) return;
   if (a.status && a.status[i] != ST_CONVERGED) {
     a.verdict[i] = V_UNCHECKED;
@@ -842,6 +846,7 @@ struct VjpArgs {
   double cond_thr;
   unsigned int* defer_count;  // FP32 mode: configurations left to the FP64 tail kernel
   int32_t* defer_idx;
+  unsigned int* clear;        // FP32 mode: the count of the next call, zeroed by the main kernel (nullptr: none)
 };
 
 // The VJP kernels keep the upstream gradient g of a lane in LDS, in the precision of the solve (a
@@ -942,6 +947,8 @@ __global__ void __launch_bounds__(64) k_vjp(VjpArgs a) {
   // the trig tile takes the iterate's place slot by slot: the one pass that reads the iterate writes it
   const auto tr = make_trig<Model, W::trig && f32>(smem, tiles);
   const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+  if constexpr (f32)
+    if (i == 0 && a.clear) *a.clear = 0u;
   if (i >= a.n) return;
   const int dof = dof_of<Model>(C);
   if (a.status[i] != ST_CONVERGED) {

@@ -362,8 +362,8 @@ struct Kin {
   // origins (42 values) for the passes after it. Longer walks would not hold them in registers. Bound by the latency of
   // the chain of frames, one or two waves per SIMD: with a walk per pass (FP64 residual, Gram, J^T y), each joint's
   // coordinate, sine coefficients and constants awaited in turn, the projection of 131,072 arm configurations with a
-  // bounded region (30 steps for 151 of them) took 305 us, so 256 us (and as many full waves as fill the card twice 7.5 us a step, 4 cycles an
-  // instruction).
+  // bounded region (30 steps for 151 of them) took 305 us, so 256 us; a step then takes a lone wave 4.9 us, two waves on
+  // a SIMD 7.5 us (4 cycles an instruction).
   static constexpr bool chain() {
     bool c = !Topo::has_com && NF == 1 && NB == 1 && NJ >= 2 && Topo::frame_link[0] == NJ - 1;
     for (int j = 0; j < NJ; ++j) c = c && Topo::parent[j] == j - 1;

@@ -21,7 +21,7 @@ struct FamilyOps {
   // check_batch's broad phase (verdicts only), whose queue check_tail finishes; null where the
   // model has no broad phase
   hipError_t (*check_broad)(const CheckArgs& a, unsigned* count, int32_t* idx, double* qbuf, int64_t cap,
-                            hipStream_t s);
+                            unsigned* clear, hipStream_t s);
   hipError_t (*vjp)(const VjpArgs& a, hipStream_t s);
   hipError_t (*vjp_tail)(const VjpArgs& a, int grid, hipStream_t s);  // FP32 mode only
   hipError_t (*vjp_exact)(const VjpxArgs& a, hipStream_t s);
@@ -59,7 +59,7 @@ struct OpsImpl {
   static hipError_t vjp_tail(const VjpArgs& a, int grid, hipStream_t s);
   static hipError_t check(const CheckArgs& a, int minsd, hipStream_t s);
   static hipError_t check_broad(const CheckArgs& a, unsigned* count, int32_t* idx, double* qbuf, int64_t cap,
-                                hipStream_t s);
+                                unsigned* clear, hipStream_t s);
   static hipError_t vjp(const VjpArgs& a, hipStream_t s);
   static hipError_t vjp_exact(const VjpxArgs& a, hipStream_t s);
   static hipError_t eval_fj(const DevProblem* P, int64_t n, const void* q, int64_t ld, void* F, void* J, hipStream_t s);

@@ -101,9 +101,10 @@ hipError_t OpsImpl<Model, IO, S>::check(const CheckArgs& a, int minsd, hipStream
 }
 template <class Model, class IO, class S>
 hipError_t OpsImpl<Model, IO, S>::check_broad(const CheckArgs& a, unsigned* count, int32_t* idx, double* qbuf,
-                                              int64_t cap, hipStream_t s) {
+                                              int64_t cap, unsigned* clear, hipStream_t s) {
   if constexpr (Model::broad_in_residual) {
-    hipLaunchKernelGGL((k_check_broad<Model, IO>), dim3(blocks_for(a.n, 256)), dim3(256), 0, s, a, count, idx, qbuf, cap);
+    hipLaunchKernelGGL((k_check_broad<Model, IO>), dim3(blocks_for(a.n, 256)), dim3(256), 0, s, a, count, idx, qbuf, cap,
+                       clear);
     return hipGetLastError();
   } else {
     return hipErrorInvalidValue;  // not in the launch table of such a model
@@ -151,7 +152,7 @@ hipError_t OpsImpl<Model, IO, S>::eval_cond(const DevProblem* P, int64_t n, cons
 #define MC_INST_CHECK(O)                                                                             \
   template hipError_t O::check_tail(const mc::ProjArgs&, int, hipStream_t);                           \
   template hipError_t O::check(const mc::CheckArgs&, int, hipStream_t);                                \
-  template hipError_t O::check_broad(const mc::CheckArgs&, unsigned*, int32_t*, double*, int64_t, hipStream_t);
+  template hipError_t O::check_broad(const mc::CheckArgs&, unsigned*, int32_t*, double*, int64_t, unsigned*, hipStream_t);
 #define MC_INST_VJP(O) template hipError_t O::vjp(const mc::VjpArgs&, hipStream_t);
 #define MC_INST_VJP_TAIL(O) template hipError_t O::vjp_tail(const mc::VjpArgs&, int, hipStream_t);
 #define MC_INST_VJP_EXACT(O) template hipError_t O::vjp_exact(const mc::VjpxArgs&, hipStream_t);
