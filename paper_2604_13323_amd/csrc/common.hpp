@@ -110,6 +110,49 @@ __device__ __forceinline__ float box_dist2(const float* c, const float4& lo, con
   return dx * dx + dy * dy + dz * dz;
 }
 
+// Lane k's value, as a scalar.
+__device__ __forceinline__ float lane_value(float x, int k) {
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), k));
+}
+// Maximum over the wave of non-negative floats (as bit patterns, which order alike; a NaN counts as the largest).
+__device__ __forceinline__ float wave_max_nonneg(float x) {
+  unsigned v = __float_as_uint(x);
+  auto step = [&](unsigned o) { v = o > v ? o : v; };
+  step(__builtin_amdgcn_update_dpp(0u, v, 0x111, 0xf, 0xf, false));  // row_shr:1, 2, 4, 8
+  step(__builtin_amdgcn_update_dpp(0u, v, 0x112, 0xf, 0xf, false));
+  step(__builtin_amdgcn_update_dpp(0u, v, 0x114, 0xf, 0xf, false));
+  step(__builtin_amdgcn_update_dpp(0u, v, 0x118, 0xf, 0xf, false));
+  step(__builtin_amdgcn_update_dpp(0u, v, 0x142, 0xa, 0xf, false));  // row_bcast:15, 31
+  step(__builtin_amdgcn_update_dpp(0u, v, 0x143, 0xc, 0xf, false));
+  return __uint_as_float(unsigned(__builtin_amdgcn_readlane(int(v), 63)));
+}
+// A ball around the live lanes' points, each with a sphere of radius r around it: centred between the first and the last
+// of them (neighbouring lanes hold neighbouring configurations), its radius grown by 1e-5 of itself and 1e-5 m, far above
+// the FP32 rounding of the distances. reaches(), reaches_box(): may the obstacle, or one in the
+// box, touch one of those spheres? (Also where a NaN is met.)
+struct WaveBall {
+  float c[3], r;
+  __device__ __forceinline__ bool reaches(const float4& ob) const {
+    const float dx = ob.x - c[0], dy = ob.y - c[1], dz = ob.z - c[2];
+    const float t = r + ob.w;
+    return !(dx * dx + dy * dy + dz * dz > t * t);
+  }
+  __device__ __forceinline__ bool reaches_box(const float4& lo, const float4& hi) const { return !(box_dist2(c, lo, hi) > r * r); }
+};
+__device__ __forceinline__ WaveBall wave_ball(const float* p, bool live, float r) {
+  WaveBall b;
+  const uint64_t m = uint64_t(__ballot(live));
+  const int first = m != 0 ? __builtin_ctzll(m) : 0, last = m != 0 ? 63 - __builtin_clzll(m) : 0;
+  float d2 = 0.f;
+  for (int k = 0; k < 3; ++k) {
+    b.c[k] = 0.5f * lane_value(p[k], first) + 0.5f * lane_value(p[k], last);
+    const float d = p[k] - b.c[k];
+    d2 += d * d;
+  }
+  b.r = (__fsqrt_rn(wave_max_nonneg(live ? d2 : 0.f)) + r) * 1.00001f + 1e-5f;
+  return b;
+}
+
 struct DevProblem {
   Consts c;
   CollConsts k;

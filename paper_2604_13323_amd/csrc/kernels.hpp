@@ -612,18 +612,23 @@ k_project_persistent(ProjArgs) {
 // most clusters are near, by the latency of the scalar reads else (four waves per SIMD: a chain's
 // coordinates, read at once, take 107 registers; five or more spill).
 // Before (groups of 4 lanes) and after, us: 65,536 humanoid configurations 26.5 -> 17.0, Digit 149 -> 107, 65,536 checked
-// humanoid configurations near the shelves 156 -> 106, 4,000 dual-arm geodesics of 4 to 128 configurations 349 -> 197,
-// 131,072 arm configurations 114 -> 55, 1,021 arm geodesics of 4 to 64 configurations 79 -> 36.
+// humanoid configurations near the shelves 156 -> 106, 4,000 dual-arm geodesics of 4 to 128 configurations 349 -> 89,
+// 131,072 arm configurations 114 -> 17, 1,021 arm geodesics of 4 to 64 configurations 79 -> 30.
 template <class Model>
 __global__ void __launch_bounds__(256, 4) k_check_lanes(ProjArgs a) {
+  __shared__ float4 slot_mem[4 * 64];  // launched with 256 threads
   const int64_t cnt = *a.chk_count;
   constexpr int NL = Model::NGEO;
   const int lane = int(threadIdx.x) & 63;
   const int wpb = int(blockDim.x) >> 6;
   const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
-  const int64_t items = (cnt + 63) / 64 * NL;
-  for (int64_t item = int64_t(blockIdx.x) * wpb + wave; item < items; item += int64_t(gridDim.x) * wpb) {
-    const int64_t grp = item / NL;
+  // Arms: link by link from the chain's end, so that a hit that one link finds spares its lane the links after it. Trees:
+  // group by group, whose coordinates (288 bytes each) stay in L2 over their 30 links.
+  constexpr bool by_link = Model::D <= Model::kGatherMaxD;
+  const int64_t groups = (cnt + 63) / 64;
+  for (int64_t item = int64_t(blockIdx.x) * wpb + wave; item < groups * NL; item += int64_t(gridDim.x) * wpb) {
+    const int64_t grp = by_link ? item % groups : item / NL;
+    const int rank = by_link ? NL - 1 - int(item / groups) : int(item % NL);
     const int64_t slot = grp * 64 + lane;
     const bool in = slot < cnt;
     const int64_t s = in ? slot : cnt - 1;
@@ -632,8 +637,9 @@ __global__ void __launch_bounds__(256, 4) k_check_lanes(ProjArgs a) {
     if (!__any(live)) continue;
     const QGlob<double> q{a.chk_q, a.defer_cap, s, Model::D};
     Rig<float> X;
-    const int l = Model::geo_frame(int(item - grp * NL), q, consts_of(a.P), X);
-    if (Model::link_hits(X, l, coll_of(a.P), obs_pad_of(a.P), live) && live) a.verdict[i] = V_HIT;  // queued as V_FREE
+    const int l = Model::geo_frame(rank, q, consts_of(a.P), X);
+    if (Model::link_hits(X, l, coll_of(a.P), obs_pad_of(a.P), live, slot_mem + wave * 64) && live)
+      a.verdict[i] = V_HIT;  // queued as V_FREE
   }
 }
 

@@ -1192,13 +1192,78 @@ struct Kin {
     return link;
   }
 
-  // Collision check of one link, one configuration per lane. Everything but the configuration is wave-uniform: the
-  // link's bound is tested against the boxes of the cluster groups and of their clusters, four boxes per scalar read,
-  // and a cluster that any lane's link reaches is taken for the whole wave, its box and all its obstacles read at once
-  // into scalar registers and tested against the link's spheres four at a time. Lanes that did not need a test run
-  // it all the same: an overlap it finds is one. (The queue keeps neighbouring configurations of a geodesic in
-  // neighbouring lanes, whose clusters are mostly the same.)
-  static __device__ __forceinline__ bool link_hits(const Rig<float>& X, int l, const CollConsts& K, const float4* pad, bool live) {
+  // Gathering pays where obstacles are scattered among an arm's links, so that a cluster's box says little (check of 4,000
+  // dual-arm geodesics 197 -> 89 us, of 131,072 arm configurations 55 -> 17, of 1,021 arm geodesics 36 -> 30). The links of the
+  // 36-DoF trees meet packed slabs, whose clusters are compact and of which more than 64 obstacles are in reach at once:
+  // there it costs (Digit 107 -> 114 us, configurations near the shelves 106 -> 115).
+  static constexpr int kGatherMaxD = 16;
+  // The obstacles within reach of the wave's copies of a link's bound (centre cb, radius r) into the wave's 64 LDS slots:
+  // the lanes test 64 cluster boxes at once against the ball around them, then the obstacles of four near clusters.
+  // Returns how many, or -1 when there are more than 64.
+  static __device__ __forceinline__ int gather(const float* cb, float r, const CollConsts& K, const float4* pad, bool live,
+                                               float4* slots) {
+    static_assert(kClusterSize == 16, "16 lanes take a cluster");
+    const int lane = int(__lane_id()), row = lane >> 4;
+    const WaveBall b = wave_ball(cb, live, r);
+    int n = 0;
+    for (int g = 0; g < K.n_clus; g += 64) {
+      const int t = g + lane < K.n_clus ? g + lane : K.n_clus - 1;
+      uint64_t near = uint64_t(__ballot(g + lane < K.n_clus && b.reaches_box(K.clus_box[2 * t], K.clus_box[2 * t + 1])));
+      while (near != 0) {
+        int c[4];
+        for (int i = 0; i < 4; ++i) {
+          c[i] = near != 0 ? __builtin_ctzll(near) : -1;
+          near &= near - 1;
+        }
+        const int mine = row == 0 ? c[0] : row == 1 ? c[1] : row == 2 ? c[2] : c[3];
+        const float4 ob = pad[(g + (mine < 0 ? c[0] : mine)) * kClusterSize + (lane & 15)];
+        const bool cand = mine >= 0 && b.reaches(ob);
+        const uint64_t m = uint64_t(__ballot(cand));
+        const int rank = n + __builtin_popcountll(m & ((uint64_t(1) << lane) - 1));
+        n += __builtin_popcountll(m);
+        if (n > 64) return -1;
+        if (cand) slots[rank] = ob;
+      }
+    }
+    return n;
+  }
+  // The link's spheres [s0, s1) against the n candidates in the slots: again only those that reach the ball around the
+  // wave's copies of a sphere are tested exactly.
+  static __device__ __forceinline__ bool candidate_hits(const Rig<float>& X, int s0, int s1, const CollConsts& K, bool live,
+                                                        const float4* slots, int n) {
+    const int lane = int(__lane_id());
+    bool hit = false;
+    if (n == 0) return hit;
+    const float4 ob = slots[lane < n ? lane : 0];
+    for (int s = s0; s < s1 && __any(live); ++s) {
+      const float4 sp = K.sph[s];
+      const float lp[3] = {sp.x, sp.y, sp.z};
+      float c[3];
+      matvec3(X.R, lp, c);
+      for (int k = 0; k < 3; ++k) c[k] += X.p[k];
+      const WaveBall b = wave_ball(c, live, sp.w);
+      uint64_t m = uint64_t(__ballot(lane < n && b.reaches(ob)));
+      while (m != 0) {
+        const int k = __builtin_ctzll(m);
+        m &= m - 1;
+        const float dx = c[0] - lane_value(ob.x, k), dy = c[1] - lane_value(ob.y, k), dz = c[2] - lane_value(ob.z, k);
+        const float rr = sp.w + lane_value(ob.w, k);
+        hit = hit || (dx * dx + dy * dy + dz * dz < rr * rr);
+      }
+      live = live && !hit;
+    }
+    return hit;
+  }
+
+  // Collision check of one link, one configuration per lane (live: the lanes to check). Everything but the configuration is
+  // wave-uniform. Arms (kGatherMaxD): where the wave's copies of the link are close together (neighbouring configurations
+  // of a geodesic), few obstacles are within reach of any of them, and gather() finds those with a lane per obstacle. Else,
+  // and where that gives more than 64, the link's bound is tested lane by lane against the boxes of the cluster groups
+  // and of their clusters, four boxes per scalar read, and a cluster that any lane's link reaches is taken for the whole
+  // wave, its box and all its obstacles read at once into scalar registers and tested against the link's spheres four at
+  // a time. Lanes that did not need a test run it all the same: an overlap it finds is one.
+  static __device__ __forceinline__ bool link_hits(const Rig<float>& X, int l, const CollConsts& K, const float4* pad, bool live,
+                                                   float4* slots) {
     using V16 = float __attribute__((ext_vector_type(16), aligned(16)));
     using V8 = float __attribute__((ext_vector_type(8), aligned(16)));
     const float4 bs = K.link_bs[l];
@@ -1208,6 +1273,10 @@ struct Kin {
     float cb[3];
     matvec3(X.R, lc, cb);
     for (int k = 0; k < 3; ++k) cb[k] += X.p[k];
+    if constexpr (D <= kGatherMaxD) {
+      const int cand = gather(cb, bs.w, K, pad, live, slots);
+      if (cand >= 0) return candidate_hits(X, s0, s1, K, live, slots, cand);
+    }
     const float r2 = bs.w * bs.w;
     auto reach = [&](const V16& v, int k) {  // box k of the two in v
       const float4 lo = make_float4(v[8 * k], v[8 * k + 1], v[8 * k + 2], 0.f);
