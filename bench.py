@@ -36,7 +36,8 @@ def log(*a):
     print(*a, file=sys.stderr, flush=True)
 
 
-PROJECTION_SOURCES = ("common.hpp", "kin.hpp", "kernels.hpp", "ops.hpp", "ops_impl.hpp", "fam_humanoid36_f32_persistent.hip")
+PROJECTION_SOURCES = ("common.hpp", "trig.hpp", "kin.hpp", "leaf.hpp", "kernels.hpp", "ops.hpp", "ops_impl.hpp",
+                      "fam_humanoid36_f32_persistent.hip")
 
 
 def source_hash() -> str:
@@ -295,7 +296,7 @@ def main():
 
     # --- the dominant kernel: the persistent projection kernel of the fused step (with its broad-phase
     # walk), its launch duration from HIP events the library records around that launch alone on the
-    # call's stream (queue reset, FP64 and exact-check tails excluded), one timed call after another
+    # call's stream (FP64 tail and exact check excluded), one timed call after another
     G.kernel_timing(True)
     for _ in range(args.warmup):
         G.project(q_in, variant="fused", out=out, **kw)
@@ -358,7 +359,7 @@ def main():
         q4, offs4, _ = build_batch(G, cfg4, torch)
         n4 = q4.shape[1]
         # the launch shape is left to the library here: this batch is larger than the lanes of the
-        # one-wave launch, so it runs in the two-wave build
+        # one-wave launch
         kw4 = dict(kw, waves_per_block=0, blocks_per_cu=0)
         o4 = G.project(q4, variant="fused", **kw4)
 

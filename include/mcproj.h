@@ -347,7 +347,7 @@ mc_status mc_set_check_lanes(mc_problem* p, int32_t lanes);
    (the persistent kernel of the fused variant, all per-geodesic launches of the plain one) and
    project_vjp / project_vjp_exact their main VJP launch with HIP events on the call's stream; mc_last_kernel_ms waits for
    the last such call and returns the time between its two events (which = 0: projection, 1: VJP).
-   The time excludes the queue reset and the FP64 and exact-check tail launches. Off by default;
+   The time excludes the FP64 tail and exact-check launches. Off by default;
    turning it on creates the events (not under stream capture). */
 mc_status mc_set_kernel_timing(mc_problem* p, int32_t on);
 mc_status mc_last_kernel_ms(const mc_problem* p, int32_t which, float* ms);

@@ -262,7 +262,7 @@ bool validate_family(const HScene& s, std::string& err) {
 
 // ---- obstacle clusters: recursive median split on the widest axis, <= kClusterSize each
 constexpr double kBoundMargin = 1e-4;  // metres added to every bound (covers FP32 rounding)
-// exact-check tail grid: workgroups of 256 per CU (its short-queue path takes up to 4 waves' work
+// exact-check grid: workgroups of 256 per CU (its short-queue path takes up to 4 waves' work
 // items per workgroup)
 constexpr int kCheckTailBlocksPerCu = 4;
 static_assert((MAXC + kGroupSize - 1) / kGroupSize <= MAXSUP, "group table too small");

@@ -2,8 +2,8 @@
 //
 // Mapping: one configuration per lane; the lane's FP64 iterate lives in LDS (a column
 // of a [D][blockDim] array, conflict-free); the kinematic constants are read with scalar
-// loads (wave-uniform, so they occupy scalar registers), the collision data is staged in
-// LDS once per workgroup; everything else is in registers. The hot
+// loads (wave-uniform, so they occupy scalar registers), as is the scene in the exact check;
+// everything else is in registers. The hot
 // loop (Alg. 2 ParallelProject with getDescentStep on one stacked block) per iteration:
 //   1. residual pass, FP64: forward kinematics, F(q), ||F||^2, and the per-block data
 //      the Jacobian columns need;
@@ -61,8 +61,8 @@ struct ProjArgs {
   int32_t* chk_idx;
   double* chk_q;
   int32_t n_sph, n_obs;   // robot and obstacle spheres (LDS size of the exact-check kernel)
-  int32_t chk_lanes;      // exact-check tail: lanes per queued configuration (0: the tuned choice; 1, 2, 4, 8, 16, 64)
-  int32_t chk_long;       // exact-check tail: lanes per configuration as tuned, with chk_lanes = 0 (2, 4, 8 or 16 on long
+  int32_t chk_lanes;      // exact check: lanes per queued configuration (0: chk_long; 1, 2, 4, 8, 16, 64)
+  int32_t chk_long;       // exact check: lanes per configuration as tuned, with chk_lanes = 0 (2, 4, 8 or 16 on long
                           // queues; 0 or 1: one lane per configuration on every queue)
 };
 
