@@ -526,7 +526,7 @@ __device__ __forceinline__ uint8_t verdict_inline(const QLds& q, const Consts& C
 // With a verdict array the collision check is fused: tree models walk the converged
 // configuration's link bounds once more in FP32 and test them against the box around the
 // obstacles, so a configuration with no link near the obstacles is FREE at once, and the others
-// are queued for the exact check (k_check_tail).
+// are queued for the exact check (k_check_lanes).
 // Dynamic LDS: projection_lds.
 template <class Model, class IO, class S, int MODE, bool TILE>
 __device__ __forceinline__ void persistent_body(double* smem) {
@@ -556,7 +556,7 @@ __device__ __forceinline__ void persistent_body(double* smem) {
       const ProjArgs& a = kernarg<ProjArgs>();
       if (pending) {
         // broad phase on the converged configurations (an FP32 walk of the link bounds)
-        a.verdict[i] = V_FREE;  // k_check_tail overwrites it with V_HIT if some part finds a hit
+        a.verdict[i] = V_FREE;  // the exact check overwrites it with V_HIT if a link hits
         if (Model::broad_flag(q, C)) a.chk_idx[queue_q<Model>(q, a.chk_count, a.chk_q, a.defer_cap)] = int32_t(i);
         pending = false;
         i = a.n_static + int64_t(atomicAdd(a.counter, 1u));
@@ -623,7 +623,7 @@ __global__ void __launch_bounds__(256, 4) k_check_lanes(ProjArgs a) {
   const int wpb = int(blockDim.x) >> 6;
   const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
   // Arms: link by link from the chain's end, so that a hit that one link finds spares its lane the links after it. Trees:
-  // group by group, whose coordinates (288 bytes each) stay in L2 over their 30 links.
+  // group by group, whose coordinates (288 bytes each) stay in L2 over their 31 links.
   constexpr bool by_link = Model::D <= Model::kGatherMaxD;
   const int64_t groups = (cnt + 63) / 64;
   for (int64_t item = int64_t(blockIdx.x) * wpb + wave; item < groups * NL; item += int64_t(gridDim.x) * wpb) {
@@ -707,7 +707,7 @@ __global__ void __launch_bounds__(256) k_check_tail(ProjArgs a, int64_t small, i
 // FP64 tail of the persistent variant: the configurations deferred by the FP32 kernel, one per
 // lane (grid-stride over the queue), continued from their stored FP64 iterate with FP64 steps. Their
 // collision check joins the persistent kernel's: broad phase here, flagged ones queued for
-// k_check_tail (a one-lane exact check in-line cost C1's tail half a millisecond).
+// the exact check (in-line, one lane each, it took half a millisecond on an arm batch of 2,089 such configurations).
 // Dynamic LDS: projection_lds.
 template <class Model, class IO, int MODE>
 __global__ void __launch_bounds__(64) k_project_tail(ProjArgs a) {
@@ -731,7 +731,7 @@ __global__ void __launch_bounds__(64) k_project_tail(ProjArgs a) {
     if (a.verdict) {
       if constexpr (Model::broad_in_residual) {
         // as in the persistent kernel: the broad phase here, the exact check of flagged
-        // configurations in k_check_tail (launched after this kernel), with its lane groups
+        // configurations in the kernel launched after this one
         if (a.check && st == ST_CONVERGED) {
           a.verdict[i] = V_FREE;
           if (Model::broad_flag(q, C)) a.chk_idx[queue_q<Model>(q, a.chk_count, a.chk_q, a.defer_cap)] = int32_t(i);
@@ -824,7 +824,7 @@ __global__ void __launch_bounds__(256) k_check(CheckArgs a) {
 // check_batch without distances, first pass: one lane per configuration, the FP32 walk of the link
 // bounds against the box around all obstacles (the same broad phase as the fused projection). A
 // configuration with no link near the box is FREE; the others are marked FREE and queued (index,
-// FP64 configuration) for k_check_tail, which overwrites the verdict of those it finds colliding.
+// FP64 configuration) for the exact check, which overwrites the verdict of those it finds colliding.
 template <class Model, class IO>
 __global__ void __launch_bounds__(256) k_check_broad(CheckArgs a, unsigned* count, int32_t* idx, double* qbuf,
                                                      int64_t cap, unsigned* clear) {
