@@ -266,6 +266,7 @@ constexpr double kBoundMargin = 1e-4;  // metres added to every bound (covers FP
 // items per workgroup)
 constexpr int kCheckTailBlocksPerCu = 4;
 static_assert((MAXC + kGroupSize - 1) / kGroupSize <= MAXSUP, "group table too small");
+static_assert(MAXC % (4 * kGroupSize) == 0, "the exact check reads the boxes of four groups at a time");
 
 void build_clusters(std::vector<std::array<double, 4>>& obs, int lo, int hi,
                     std::vector<std::array<double, 4>>& cl, std::vector<std::array<int, 2>>& rg) {
@@ -1102,7 +1103,10 @@ mc_status mc_problem_create(const void* blob, size_t nbytes, mc_problem** out) {
   K.n_clus = int(cl.size());
   std::vector<float4> obs_f(obs.size());
   for (size_t i = 0; i < obs.size(); ++i) obs_f[i] = make_float4(float(obs[i][0]), float(obs[i][1]), float(obs[i][2]), float(obs[i][3]));
-  std::vector<float4> pad_f(cl.size() * kClusterSize, make_float4(1e18f, 1e18f, 1e18f, 0.f));
+  // (slots for every cluster of the last read of four groups: a configuration with NaN coordinates is within reach of the
+  // empty boxes too, and the slots of their clusters are then read, though none of their obstacles is tested)
+  const size_t pad_clusters = (cl.size() + 4 * kGroupSize - 1) / (4 * kGroupSize) * (4 * kGroupSize);
+  std::vector<float4> pad_f(pad_clusters * kClusterSize, make_float4(1e18f, 1e18f, 1e18f, 0.f));
   for (size_t i = 0; i < cl.size(); ++i)
     for (int o = rg[i][0]; o < rg[i][1]; ++o) pad_f[i * kClusterSize + size_t(o - rg[i][0])] = obs_f[o];
   for (int i = 0; i < MAXC; ++i) {

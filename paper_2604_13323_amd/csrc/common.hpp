@@ -157,7 +157,8 @@ struct DevProblem {
   Consts c;
   CollConsts k;
   const float4* obs;             // obstacles (x, y, z, r), grouped by cluster, n_obs of them
-  const float4* obs_pad;         // the same, kClusterSize slots per cluster (spheres out of reach fill them up)
+  const float4* obs_pad;         // the same, kClusterSize slots per cluster, up to the end of the last four groups
+                                 // (spheres out of reach fill them up)
   unsigned long long* fallback_counter;
 };
 
