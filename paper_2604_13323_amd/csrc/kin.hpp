@@ -729,7 +729,7 @@ struct Kin {
     const double f0 = inside ? 0.0 : (on_edge ? bnx * dx + bny * dy : dx);
     const double f1 = vtx ? dy : 0.0;
     const double h0 = inside ? 0.0 : (on_edge ? bnx : 1.0);
-    const double h1 = on_edge ? bny : 0.0;
+    const double h1 = !inside && on_edge ? bny : 0.0;
     const double h3 = vtx ? 1.0 : 0.0;
     const uint32_t dm = inside ? 3u : (on_edge ? 2u : 0u);
     F[r0] = to_step<S>(f0);

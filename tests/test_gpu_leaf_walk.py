@@ -16,16 +16,9 @@ torch = pytest.importorskip("torch")
 SCENES = dict(humanoid=lambda: S.humanoid36_scene(3), digit=lambda: S.digit36_scene(5), dual=lambda: S.dual14_rel_scene(2))
 
 
-# Inside the support polygon next to a slanted edge, hull_rows keeps the edge normal's second component in the row map
-# although the row is dropped (h1 lacks h0's inside test): a damped extra row, 1e-3 of the step, in the root-to-leaf walk
-# as in this one. It is kept, with the outputs that rest on it.
-HULL = pytest.mark.xfail(strict=True, reason="row map of a dropped support-polygon row is not zero inside near a slanted edge")
-
-
 @pytest.mark.parametrize("lam", [0.0, 1e-2])
 @pytest.mark.parametrize("name,spread,turns", [
-    pytest.param(name, spread, turns, marks=HULL if name == "digit" and spread > 0.1 else [])
-    for name in sorted(SCENES) for spread, turns in [(0.02, 0), (0.4, 0), (0.4, 40)]])
+    (name, spread, turns) for name in sorted(SCENES) for spread, turns in [(0.02, 0), (0.4, 0), (0.4, 40)]])
 def test_one_fp64_step_matches_oracle(name, spread, turns, lam):
     """Tolerance: both sides solve the same system in FP64; the forward error is kappa_2(G) 2^-53 times a small constant
     and the step, so 1e-9 (1 + |step|) where kappa_2 < 1e5, plus the 2^-53 |q| of angles turned by up to 40 turns times
