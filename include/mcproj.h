@@ -337,10 +337,12 @@ mc_status mc_queue_counts(const mc_problem* p, uint32_t counts[4]);
 
 /* mc_set_check_lanes — lanes per configuration of the exact collision check that project_batch
    (fused variant), extend_batch and check_batch run on the configurations their broad phase flags
-   (Sec. IV-B, the collision test of every projected configuration). 0 (the default): one
-   (or, on queues longer than 4 per launch workgroup, the group size mc_autotune_project chose); 1, 2, 4, 8, 16 or
-   64: that many on every queue. Groups of 2 lanes exist for families of at most 16 coordinates and run only
-   where the scene's staged spheres leave LDS room for them (else 4). Verdicts do not depend on it. MC_ERR_INVALID_ARG for other values. */
+   (Sec. IV-B, the collision test of every projected configuration). 0 (the default): by scene and batch, one, or
+   on queues longer than 4 per launch workgroup the group size mc_autotune_project chose (short ones then take 64); the library
+   takes groups of 4 (64 on short queues) for an arm of at most 8 joints in a crowded scene, and 64 for the 36-DoF
+   families among more than 1,024 obstacles in batches of 257 to 4 per launch workgroup. 1, 2, 4, 8, 16 or 64: that many on every
+   queue. Groups of 2 lanes exist for families of at most 16 coordinates and run only where the scene's staged spheres leave
+   LDS room for them (else 4). Verdicts do not depend on it. MC_ERR_INVALID_ARG for other values. */
 mc_status mc_set_check_lanes(mc_problem* p, int32_t lanes);
 
 /* mc_set_kernel_timing — diagnostic: when on, project_batch brackets its main projection launch

@@ -62,8 +62,8 @@ struct ProjArgs {
   double* chk_q;
   int32_t n_sph, n_obs;   // robot and obstacle spheres (LDS size of the exact-check kernel)
   int32_t chk_lanes;      // exact check: lanes per queued configuration (0: chk_long; 1, 2, 4, 8, 16, 64)
-  int32_t chk_long;       // exact check: lanes per configuration as tuned, with chk_lanes = 0 (2, 4, 8 or 16 on long
-                          // queues; 0 or 1: one lane per configuration on every queue)
+  int32_t chk_long;       // exact check: lanes per configuration as tuned or by the scene, with chk_lanes = 0 (2, 4, 8 or 16
+                          // on long queues and 64 on short ones; 0 or 1: one lane per configuration on every queue)
 };
 
 constexpr int ST_DEFER = -2;  // internal: continue this configuration with FP64 steps
@@ -622,23 +622,37 @@ __global__ void __launch_bounds__(256, 4) k_check_lanes(ProjArgs a) {
   const int lane = int(threadIdx.x) & 63;
   const int wpb = int(blockDim.x) >> 6;
   const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
-  // Arms: link by link from the chain's end, so that a hit that one link finds spares its lane the links after it. Trees:
-  // group by group, whose coordinates (288 bytes each) stay in L2 over their 31 links.
-  constexpr bool by_link = Model::D <= Model::kGatherMaxD;
-  const int64_t groups = (cnt + 63) / 64;
-  for (int64_t item = int64_t(blockIdx.x) * wpb + wave; item < groups * NL; item += int64_t(gridDim.x) * wpb) {
-    const int64_t grp = by_link ? item % groups : item / NL;
-    const int rank = by_link ? NL - 1 - int(item / groups) : int(item % NL);
-    const int64_t slot = grp * 64 + lane;
+  // (32 bits: the queue holds fewer than 2^31 configurations, 2^25 groups of at most 36 links)
+  const uint32_t groups = uint32_t((cnt + 63) / 64), waves = gridDim.x * uint32_t(wpb);
+  // Short queues: a link's clusters over up to 64 waves, as long as the launch has waves for it (trees: two rounds of
+  // them, their links differ in work) and the scene clusters. Unsplit, a wave of a short queue tested every near cluster in
+  // turn: 64 arm configurations among 200 scattered obstacles 31 us (17 split; a wave per configuration took 18), 365 of 512
+  // humanoid configurations near the shelves 82 us (35; 44).
+  const int n_clus = coll_of(a.P).n_clus;
+  const uint32_t room = Model::D <= Model::kGatherMaxD ? waves : 2 * waves;
+  int split = 0;  // log2
+  while (split < 6 && (1 << split) < n_clus && ((groups * NL) << (split + 1)) <= room) ++split;
+  uint64_t every = ~uint64_t(0);  // bits 0, 2^split, 2 * 2^split, ...
+  if (split > 0) {
+    every = 1;
+    for (int k = 1 << split; k < 64; k *= 2) every |= every << k;
+  }
+  // Link by link from the last one (the chains' ends come late), so that a hit that one link finds spares its lane the links
+  // after it: 65,536 humanoid configurations among 2,000 scattered obstacles 1,064 us group by group, 236 so.
+  for (uint32_t item = blockIdx.x * uint32_t(wpb) + uint32_t(wave); item < ((groups * NL) << split); item += waves) {
+    const uint32_t it = item >> split, part = item & ((1u << split) - 1);
+    const uint32_t grp = it % groups;
+    const int rank = NL - 1 - int(it / groups);
+    const int64_t slot = int64_t(grp) * 64 + lane;
     const bool in = slot < cnt;
     const int64_t s = in ? slot : cnt - 1;
     const int64_t i = a.chk_idx[s];
-    const bool live = in && a.verdict[i] != V_HIT;  // another link may have hit already
+    const bool live = in && a.verdict[i] != V_HIT;  // another item may have found a hit already
     if (!__any(live)) continue;
     const QGlob<double> q{a.chk_q, a.defer_cap, s, Model::D};
     Rig<float> X;
     const int l = Model::geo_frame(rank, q, consts_of(a.P), X);
-    if (Model::link_hits(X, l, coll_of(a.P), obs_pad_of(a.P), live, slot_mem + wave * 64) && live)
+    if (Model::link_hits(X, l, coll_of(a.P), obs_pad_of(a.P), live, slot_mem + wave * 64, every << part) && live)
       a.verdict[i] = V_HIT;  // queued as V_FREE
   }
 }

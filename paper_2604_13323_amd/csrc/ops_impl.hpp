@@ -64,14 +64,19 @@ hipError_t OpsImpl<Model, IO, S>::check_tail(const ProjArgs& a, int grid, hipStr
   if constexpr (!Model::broad_in_residual) {
     return hipErrorInvalidValue;  // not in the launch table of such a model
   } else {
-    if (a.chk_lanes == 1 || (a.chk_lanes == 0 && a.chk_long <= 1)) {
+    // short queues: a wave (or part of one configuration's links) per work item, one pass of
+    // `small` work items over 4 waves per workgroup
+    const int64_t small = int64_t(grid) * 4;
+    // Trees among more than 64 clusters, in batches whose queue is short: k_check_tail's wave per configuration, whose lanes
+    // share the many near clusters. Check of 4,096 humanoid configurations around 2,000 shelf spheres (us, wave per
+    // configuration and lanes): 100 and 130, along geodesics 94 and 89; 512 among 2,000 scattered ones 52 and 66; 64 configurations
+    // 47 and 40, 512 among 500 shelf spheres 42 and 35.
+    const bool waves = Model::D > Model::kGatherMaxD && a.n_obs > 64 * kClusterSize && a.n > 256 && a.n <= small;
+    if (a.chk_lanes == 1 || (a.chk_lanes == 0 && a.chk_long <= 1 && !waves)) {
       hipLaunchKernelGGL((k_check_lanes<Model>), dim3(grid), dim3(256), 0, s, a);
       return hipGetLastError();
     }
     const size_t stage = size_t(a.n_sph + a.n_obs) * 16;
-    // short queues: a wave (or part of one configuration's links) per work item, one pass of
-    // `small` work items over 4 waves per workgroup
-    const int64_t small = int64_t(grid) * 4;
     // groups of 2 lanes only where their staged configurations fit beside the spheres in a quarter of the
     // CU's LDS; the LDS covers 256 / min_lanes groups (or the wave path's slots, if more)
     int min_lanes = 4;

@@ -43,7 +43,7 @@ def test_nan_configurations_among_finite_ones(family, n_obs):
         qn[40, sc.d // 3] = np.nan  # one coordinate: the links behind it
         qd = to_dev(qn, dtype)
         got = {}
-        for lanes in (0, 4, 64):
+        for lanes in (0, 1, 4, 64):
             G.set_check_lanes(lanes)
             got[lanes] = from_dev(G.check(qd)).astype(int)
         G.set_check_lanes(0)
@@ -54,5 +54,5 @@ def test_nan_configurations_among_finite_ones(family, n_obs):
         assert (got[0][out] == vo[out]).all()
         whole = [0, 3, 63, 90, 130]
         assert (got[0][whole] == 0).all()
-        for lanes in (4, 64):
+        for lanes in (1, 4, 64):
             assert (got[lanes] == got[0]).all(), lanes
