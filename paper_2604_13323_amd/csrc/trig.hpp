@@ -6,7 +6,7 @@
 namespace mc {
 
 // Sine and cosine of k pi / 32, k = 0 .. 63 (correctly rounded).
-static __constant__ double kSinTab[64][2] = {
+constexpr double kSinTab[64][2] = {
     {0.0, 1.0}, {0.0980171403295606, 0.9951847266721969},
     {0.19509032201612828, 0.9807852804032304}, {0.2902846772544624, 0.9569403357322088},
     {0.3826834323650898, 0.9238795325112867}, {0.47139673682599764, 0.881921264348355},
@@ -57,11 +57,17 @@ using SinTabP = const __attribute__((address_space(3))) double*;
 // its series to r^15 and r^16.
 // In two parts, so that other work can stand between the read and its use: the entry (and k), then the rest.
 using SinTabV = double __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ SinTabV sin_tab_entry(double x, SinTabP tab, double& k) {
-  k = __builtin_rint(x * 10.185916357881302);
-  return *(const __attribute__((address_space(3))) SinTabV*)(tab + 2 * (int(k) & 63));
+// x 32/pi is rounded to the whole number k by adding 1.5 2^52, whose low bits are then k's (|k| < 2^51; a conversion to 32
+// bits ended at |x| = 2.1e8).
+__host__ __device__ __forceinline__ int sin_tab_index(double x, double& k) {
+  const double t = __builtin_fma(x, 10.185916357881302, 6755399441055744.0);
+  k = t - 6755399441055744.0;
+  return int(__builtin_bit_cast(uint64_t, t)) & 63;
 }
-__device__ __forceinline__ void sincos_finish(double x, double k, SinTabV t, double& s, double& c) {
+__device__ __forceinline__ SinTabV sin_tab_entry(double x, SinTabP tab, double& k) {
+  return *(const __attribute__((address_space(3))) SinTabV*)(tab + 2 * sin_tab_index(x, k));
+}
+__host__ __device__ __forceinline__ void sincos_finish(double x, double k, SinTabV t, double& s, double& c) {
   double r = __builtin_fma(-k, 0.09817477042468103, x);
   r = __builtin_fma(-k, 3.827021247335479e-18, r);
   const double r2 = r * r;
