@@ -618,6 +618,7 @@ template <class Model>
 __global__ void __launch_bounds__(256, 4) k_check_lanes(ProjArgs a) {
   __shared__ float4 slot_mem[4 * 64];  // launched with 256 threads
   const int64_t cnt = *a.chk_count;
+  if (cnt == 0) return;
   constexpr int NL = Model::NGEO;
   const int lane = int(threadIdx.x) & 63;
   const int wpb = int(blockDim.x) >> 6;

@@ -1199,9 +1199,10 @@ struct Kin {
   static constexpr int kGatherMaxD = 16;
   // The obstacles within reach of the wave's copies of a link's bound (centre cb, radius r) into the wave's 64 LDS slots:
   // the lanes test 64 cluster boxes at once against the ball around them, then the obstacles of four near clusters.
-  // Returns how many, or -1 when there are more than 64, or more than four for each near cluster: the ball then excludes too
-  // little, and a candidate costs more than an obstacle of a cluster (16,384 uncorrelated arm configurations among 200
-  // obstacles 39 us without this line, 29 with it; geodesics of the dual arm are below it).
+  // Returns how many, or -1 when there are more than 64, or more than 16 and four for each near cluster: the ball then excludes
+  // too little, and a candidate costs more than an obstacle of a cluster (16,384 uncorrelated arm configurations among 200
+  // obstacles 39 us without this line, 29 with it; geodesics of the dual arm are below it). Up to 16 cost less than the
+  // walk over the boxes (64 dual-arm configurations of a geodesic 13.7 us, 16.1 without this exception).
   static __device__ __forceinline__ int gather(const float* cb, float r, const CollConsts& K, const float4* pad, bool live,
                                                float4* slots, uint64_t part) {
     static_assert(kClusterSize == 16, "16 lanes take a cluster");
@@ -1224,7 +1225,7 @@ struct Kin {
         const uint64_t m = uint64_t(__ballot(cand));
         const int rank = n + __builtin_popcountll(m & ((uint64_t(1) << lane) - 1));
         n += __builtin_popcountll(m);
-        if (n > 64 || n > most) return -1;
+        if (n > 64 || (n > 16 && n > most)) return -1;
         if (cand) slots[rank] = ob;
       }
     }
