@@ -1269,8 +1269,9 @@ struct Kin {
   // part: of every 64 clusters, those to test.
   static __device__ __forceinline__ bool link_hits(const Rig<float>& X, int l, const CollConsts& K, const float4* pad, bool live,
                                                    float4* slots, uint64_t part) {
-    using V16 = float __attribute__((ext_vector_type(16), aligned(16)));
-    using V8 = float __attribute__((ext_vector_type(8), aligned(16)));
+    typedef float V16 __attribute__((ext_vector_type(16), aligned(16)));  // (an alias declaration would drop the alignment)
+    typedef float V8 __attribute__((ext_vector_type(8), aligned(16)));
+    static_assert(alignof(V16) == alignof(float4) && alignof(V8) == alignof(float4), "read from arrays of float4");
     const float4 bs = K.link_bs[l];
     const int s0 = K.sph_begin[l], s1 = K.sph_begin[l + 1];
     if (bs.w < 0.f) return false;

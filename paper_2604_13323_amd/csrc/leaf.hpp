@@ -174,7 +174,9 @@ struct Leaf {
   // Constants of the joints of group g, with wide scalar loads.
   template <class T, int g>
   static __device__ __forceinline__ void load_consts(JD<T>* r, Frames<T>& fr, const TP<T>& P0) {
-    using V8 = T __attribute__((ext_vector_type(8)));
+    // (V8 is read behind the first four elements of a rotated joint's sixteen, which start at a multiple of 64 bytes)
+    typedef T V8 __attribute__((ext_vector_type(8), aligned(16)));  // (an alias declaration would drop the alignment)
+    static_assert(alignof(V8) <= 4 * sizeof(T), "V8 is read at c + 4");
     using V4 = T __attribute__((ext_vector_type(4)));
     using V2 = T __attribute__((ext_vector_type(2)));
     const TP<T>& P = fresh_const(P0);
