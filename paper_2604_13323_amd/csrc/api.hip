@@ -874,9 +874,9 @@ struct mc_problem {
   mutable int64_t defer_cap = 0;
   mutable int32_t* vjp_idx = nullptr;
   mutable int64_t vjp_cap = 0;
-  // resident workgroups per CU of the persistent kernel, by (FP64 mode, waves per block = 1, 2, 4);
+  // resident workgroups per CU of the persistent kernel, by (FP64 mode, outer step form, waves per block = 1, 2, 4);
   // queried once, so later calls (and calls under stream capture) make no runtime query
-  mutable int occ[2][3] = {{0, 0, 0}, {0, 0, 0}};
+  mutable int occ[2][2][3] = {};
   // launch shape stored by mc_autotune_project, by (FP64 mode, cyclic mode); waves_per_block 0 = none
   mc_launch_shape tuned[2][2] = {{{0, 0, 0}, {0, 0, 0}}, {{0, 0, 0}, {0, 0, 0}}};
   // mc_set_check_lanes: lanes per configuration of the exact check (0: check_long, or one)
@@ -1370,11 +1370,12 @@ static mc_status project_impl(const mc_problem* p, int64_t n, const void* q_in, 
       wpb = ts.waves_per_block;
       bpc = ts.blocks_per_cu;
     }
-    while (wpb > 1 && ops->lds_bytes(64 * wpb, cyc ? 1 : 0) > p->max_lds_per_block) wpb >>= 1;
+    const int mode = cyc ? CYCLIC : opts->step_form ? OUTER : STACKED;
+    while (wpb > 1 && ops->lds_bytes(64 * wpb, mode) > p->max_lds_per_block) wpb >>= 1;
     const int block = 64 * wpb;
     if (bpc <= 0) {
-      int& c = p->occ[ops->f64][wpb == 1 ? 0 : wpb == 2 ? 1 : 2];
-      if (c <= 0) c = ops->persistent_blocks_per_cu(block);  // registers bound it, not LDS
+      int& c = p->occ[ops->f64][mode == OUTER][wpb == 1 ? 0 : wpb == 2 ? 1 : 2];
+      if (c <= 0) c = ops->persistent_blocks_per_cu(block, mode);
       bpc = c;
     }
     int64_t grid = int64_t(p->n_cu) * bpc;

@@ -596,7 +596,7 @@ __device__ __forceinline__ void persistent_body(double* smem) {
 
 
 template <class Model, class S, int MODE>
-constexpr int persist_waves_v = std::is_same<S, float>::value && MODE == STACKED ? PersistWaves<Model>::value : 1;
+constexpr int persist_waves_v = std::is_same<S, float>::value && MODE != CYCLIC ? PersistWaves<Model>::value : 1;
 
 template <class Model, class IO, class S, int MODE>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(persist_waves_v<Model, S, MODE>)))

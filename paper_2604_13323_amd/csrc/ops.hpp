@@ -28,8 +28,9 @@ struct FamilyOps {
   hipError_t (*eval_fj)(const DevProblem* P, int64_t n, const void* q, int64_t ld, void* F, void* J, hipStream_t s);
   hipError_t (*eval_cond)(const DevProblem* P, int64_t n, const void* q, int64_t ld, double lambda, void* kappa,
                           hipStream_t s);
-  int (*persistent_blocks_per_cu)(int block);
-  size_t (*lds_bytes)(int block, int cyclic);  // dynamic LDS of the persistent kernel
+  // of the persistent kernel's build for a mode (STACKED, CYCLIC, OUTER)
+  int (*persistent_blocks_per_cu)(int block, int mode);
+  size_t (*lds_bytes)(int block, int mode);  // dynamic LDS
 };
 
 inline unsigned blocks_for(int64_t n, int block) { return unsigned((n + block - 1) / block); }
@@ -42,13 +43,14 @@ constexpr int kCheckLanes = 4;       // check_batch: lanes per configuration
 template <class Model, class IO, class S>
 struct OpsImpl {
   static size_t tile_bytes(int block) { return size_t(Model::D) * sizeof(double) * size_t(block); }
-  static size_t lds_bytes(int block, int cyclic) {
-    return cyclic && Model::NBLK > 1 ? projection_lds<Model, CYCLIC, kTrigTile<Model, S, CYCLIC>>(block)
-                                     : projection_lds<Model, STACKED, kTrigTile<Model, S, STACKED>>(block);
+  static size_t lds_bytes(int block, int mode) {
+    return mode == CYCLIC && Model::NBLK > 1 ? projection_lds<Model, CYCLIC, kTrigTile<Model, S, CYCLIC>>(block)
+           : mode == OUTER                   ? projection_lds<Model, OUTER, kTrigTile<Model, S, OUTER>>(block)
+                                             : projection_lds<Model, STACKED, kTrigTile<Model, S, STACKED>>(block);
   }
   static constexpr bool kOuter = Model::D <= kOuterMaxD;  // the outer step form has its own builds
   static hipError_t project_persistent(const ProjArgs& a, int grid, int block, hipStream_t s);
-  static int persistent_blocks_per_cu(int block);
+  static int persistent_blocks_per_cu(int block, int mode);
   // cyclic mode (models with several constraint blocks): a second LDS tile holds the iterate at
   // the start of each iteration
   static hipError_t project_persistent_cyclic(const ProjArgs& a, int grid, int block, hipStream_t s);

@@ -11,24 +11,26 @@ template <class Model, class IO, class S>
 hipError_t OpsImpl<Model, IO, S>::project_persistent(const ProjArgs& a, int grid, int block, hipStream_t s) {
   if constexpr (kOuter) {
     if (a.outer) {
-      hipLaunchKernelGGL((k_project_persistent<Model, IO, S, OUTER>), dim3(grid), dim3(block), lds_bytes(block, 0), s, a);
+      hipLaunchKernelGGL((k_project_persistent<Model, IO, S, OUTER>), dim3(grid), dim3(block), lds_bytes(block, OUTER), s, a);
       return hipGetLastError();
     }
   }
-  hipLaunchKernelGGL((k_project_persistent<Model, IO, S, STACKED>), dim3(grid), dim3(block), lds_bytes(block, 0), s, a);
+  hipLaunchKernelGGL((k_project_persistent<Model, IO, S, STACKED>), dim3(grid), dim3(block), lds_bytes(block, STACKED), s, a);
   return hipGetLastError();
 }
 template <class Model, class IO, class S>
-int OpsImpl<Model, IO, S>::persistent_blocks_per_cu(int block) {
+int OpsImpl<Model, IO, S>::persistent_blocks_per_cu(int block, int mode) {
   int nb = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, reinterpret_cast<const void*>(&k_project_persistent<Model, IO, S, STACKED>),
-                                                   block, lds_bytes(block, 0)) != hipSuccess)
+  const void* kernel = reinterpret_cast<const void*>(&k_project_persistent<Model, IO, S, STACKED>);
+  if constexpr (kOuter)
+    if (mode == OUTER) kernel = reinterpret_cast<const void*>(&k_project_persistent<Model, IO, S, OUTER>);
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, kernel, block, lds_bytes(block, mode == OUTER ? OUTER : STACKED)) != hipSuccess)
     return 1;
   return nb > 0 ? nb : 1;
 }
 template <class Model, class IO, class S>
 hipError_t OpsImpl<Model, IO, S>::project_persistent_cyclic(const ProjArgs& a, int grid, int block, hipStream_t s) {
-  hipLaunchKernelGGL((k_project_persistent<Model, IO, S, CYCLIC>), dim3(grid), dim3(block), lds_bytes(block, 1), s, a);
+  hipLaunchKernelGGL((k_project_persistent<Model, IO, S, CYCLIC>), dim3(grid), dim3(block), lds_bytes(block, CYCLIC), s, a);
   return hipGetLastError();
 }
 template <class Model, class IO, class S>
@@ -40,11 +42,11 @@ template <class Model, class IO, class S>
 hipError_t OpsImpl<Model, IO, S>::project_plain(const ProjArgs& a, hipStream_t s) {
   if constexpr (kOuter) {
     if (a.outer) {
-      hipLaunchKernelGGL((k_project_plain<Model, IO, S, OUTER>), dim3(blocks_for(a.n, 64)), dim3(64), lds_bytes(64, 0), s, a);
+      hipLaunchKernelGGL((k_project_plain<Model, IO, S, OUTER>), dim3(blocks_for(a.n, 64)), dim3(64), lds_bytes(64, OUTER), s, a);
       return hipGetLastError();
     }
   }
-  hipLaunchKernelGGL((k_project_plain<Model, IO, S, STACKED>), dim3(blocks_for(a.n, 64)), dim3(64), lds_bytes(64, 0), s, a);
+  hipLaunchKernelGGL((k_project_plain<Model, IO, S, STACKED>), dim3(blocks_for(a.n, 64)), dim3(64), lds_bytes(64, STACKED), s, a);
   return hipGetLastError();
 }
 template <class Model, class IO, class S>
@@ -148,7 +150,7 @@ hipError_t OpsImpl<Model, IO, S>::eval_cond(const DevProblem* P, int64_t n, cons
 // kernel it launches.
 #define MC_INST_PERSISTENT(O)                                                                        \
   template hipError_t O::project_persistent(const mc::ProjArgs&, int, int, hipStream_t);             \
-  template int O::persistent_blocks_per_cu(int);
+  template int O::persistent_blocks_per_cu(int, int);
 #define MC_INST_PERSISTENT_CYCLIC(O) \
   template hipError_t O::project_persistent_cyclic(const mc::ProjArgs&, int, int, hipStream_t);
 #define MC_INST_TAIL_CYCLIC(O) template hipError_t O::project_tail_cyclic(const mc::ProjArgs&, int, hipStream_t);
