@@ -319,15 +319,19 @@ mc_status extend_batch(const mc_problem* p, int64_t E, const void* q_start, cons
                        const mc_project_opts* opts, void* q_out, int64_t ld_out, int8_t* result,
                        int32_t* particle, int32_t* n_points, void* stream);
 
-/* mc_eval_condition — diagnostic: the condition estimate that decides the FP32 -> FP64 switch,
-   kappa_est = (max L_ii / min L_ii)^2 of the Cholesky factor of J J^T + lambda I on the scene's rows
-   (MC_F32: FP32 Jacobian columns, Gram and factorisation; MC_F64: FP64), or +inf where the
-   factorisation fails. The kernels of the dual-arm and 36-DoF families take the estimate in the rows
-   they work in, each pose block's body twist, which are these turned by the pose and, in the angular
-   rows, multiplied by an inverse SO(3) Jacobian: the same singular values up to that factor (1 at a
-   zero rotation error). q [d][ld] and kappa [n] are of dtype. */
+/* mc_eval_condition — diagnostic: the condition estimate kappa_est = (max L_ii / min L_ii)^2 of the
+   Cholesky factor of J J^T + lambda I on the scene's rows (MC_F32: FP32 Jacobian columns, Gram and
+   factorisation; MC_F64: FP64), or +inf where the factorisation fails. q [d][ld] and kappa [n] are of dtype. */
 mc_status mc_eval_condition(const mc_problem* p, int64_t n, const void* q, int64_t ld, mc_dtype dtype,
                             double lambda, void* kappa, void* stream);
+
+/* mc_eval_step_condition — diagnostic: the same estimate in the rows that the projection kernels work in,
+   as it decides the FP32 -> FP64 switch of a stacked step (fp64_cond_threshold). The dual-arm and 36-DoF
+   families work in each pose block's body twist: the scene's rows turned by the pose and, in the angular
+   rows, multiplied by the right SO(3) Jacobian of the rotation error (lambda I goes along). The other
+   families work in the scene's rows. */
+mc_status mc_eval_step_condition(const mc_problem* p, int64_t n, const void* q, int64_t ld, mc_dtype dtype,
+                                 double lambda, void* kappa, void* stream);
 
 /* mc_queue_counts — diagnostic: the problem's four device queue counters after the last call
    (synchronises the device): [0] work items taken from the persistent kernel's queue beyond the

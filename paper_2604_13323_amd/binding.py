@@ -57,7 +57,7 @@ EXPORTS = ["mc_default_opts", "mc_problem_create", "mc_problem_destroy", "mc_pro
            "interpolate_geodesics", "path_length_grad", "mc_eval_residual_jacobian", "mc_fallback_count", "extend_batch",
            "mc_eval_condition", "mc_queue_counts", "mc_autotune_candidates", "mc_autotune_project", "mc_tuned_shape",
            "mc_set_kernel_timing", "mc_last_kernel_ms", "project_batch_noalloc", "project_vjp_exact",
-           "mc_set_check_lanes"]
+           "mc_set_check_lanes", "mc_eval_step_condition"]
 
 
 def lib():
@@ -90,7 +90,7 @@ def lib():
     L.mc_fallback_count.argtypes = [P, ctypes.c_int, ctypes.POINTER(ctypes.c_uint64)]
     L.extend_batch.argtypes = [P, I64, P, P, I64, P, ctypes.POINTER(ExtendOpts), ctypes.POINTER(Opts), P, I64, P, P,
                                P, P]
-    L.mc_eval_condition.argtypes = [P, I64, P, I64, ctypes.c_int, ctypes.c_double, P, P]
+    L.mc_eval_condition.argtypes = L.mc_eval_step_condition.argtypes = [P, I64, P, I64, ctypes.c_int, ctypes.c_double, P, P]
     L.mc_queue_counts.argtypes = [P, ctypes.POINTER(ctypes.c_uint32)]
     L.mc_autotune_candidates.argtypes = [ctypes.POINTER(LaunchShape)]
     L.mc_autotune_candidates.restype = I32
@@ -341,13 +341,14 @@ class Problem:
                "mc_eval_residual_jacobian")
         return F, J
 
-    def condition(self, q: torch.Tensor, lam=0.0):
-        """The kernels' condition estimate (max L_ii / min L_ii)^2 of J J^T + lam I at every column of q
-        (+inf where the factorisation fails), in q's precision mode."""
+    def condition(self, q: torch.Tensor, lam=0.0, step_rows=False):
+        """The condition estimate (max L_ii / min L_ii)^2 of J J^T + lam I at every column of q (+inf where the
+        factorisation fails), in q's precision mode: on the scene's rows, or with step_rows in the rows that the
+        projection kernels decide on (fp64_cond_threshold)."""
         n, ld = _soa(q, self.d, "condition")
         k = torch.empty(n, dtype=q.dtype, device=q.device)
-        _check(lib().mc_eval_condition(self._h, n, _ptr(q), ld, _dtype_code(q), float(lam), _ptr(k), _stream()),
-               "mc_eval_condition")
+        name = "mc_eval_step_condition" if step_rows else "mc_eval_condition"
+        _check(getattr(lib(), name)(self._h, n, _ptr(q), ld, _dtype_code(q), float(lam), _ptr(k), _stream()), name)
         return k
 
     def queue_counts(self):

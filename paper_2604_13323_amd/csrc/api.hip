@@ -1801,20 +1801,31 @@ mc_status extend_batch(const mc_problem* p, int64_t E, const void* q_start, cons
                             particle, n_points, lmax, s);
 }
 
+static mc_status eval_condition(const char* who, const mc_problem* p, int64_t n, const void* q, int64_t ld, mc_dtype dtype,
+                                double lambda, int step_rows, void* kappa, void* stream) {
+  g_err.clear();
+  const std::string w(who);
+  if (!p) return fail(MC_ERR_INVALID_ARG, w + ": null problem");
+  if (n < 0) return fail(MC_ERR_INVALID_ARG, w + ": n < 0");
+  if (dtype != MC_F32 && dtype != MC_F64) return fail(MC_ERR_INVALID_ARG, w + ": bad dtype");
+  if (!(lambda >= 0) || !std::isfinite(lambda)) return fail(MC_ERR_INVALID_ARG, w + ": lambda must be >= 0");
+  if (n == 0) return MC_OK;
+  if (!q || !kappa) return fail(MC_ERR_INVALID_ARG, w + ": null array");
+  if (ld < n) return fail(MC_ERR_INVALID_ARG, w + ": ld < n");
+  const FamilyOps* ops = ops_for(p->family, dtype == MC_F64);
+  hipError_t e = ops->eval_cond(p->dev, n, q, ld, lambda, step_rows, kappa, static_cast<hipStream_t>(stream));
+  if (e != hipSuccess) return hip_fail(e, (w + ": launch").c_str());
+  return MC_OK;
+}
+
 mc_status mc_eval_condition(const mc_problem* p, int64_t n, const void* q, int64_t ld, mc_dtype dtype, double lambda,
                             void* kappa, void* stream) {
-  g_err.clear();
-  if (!p) return fail(MC_ERR_INVALID_ARG, "mc_eval_condition: null problem");
-  if (n < 0) return fail(MC_ERR_INVALID_ARG, "mc_eval_condition: n < 0");
-  if (dtype != MC_F32 && dtype != MC_F64) return fail(MC_ERR_INVALID_ARG, "mc_eval_condition: bad dtype");
-  if (!(lambda >= 0) || !std::isfinite(lambda)) return fail(MC_ERR_INVALID_ARG, "mc_eval_condition: lambda must be >= 0");
-  if (n == 0) return MC_OK;
-  if (!q || !kappa) return fail(MC_ERR_INVALID_ARG, "mc_eval_condition: null array");
-  if (ld < n) return fail(MC_ERR_INVALID_ARG, "mc_eval_condition: ld < n");
-  const FamilyOps* ops = ops_for(p->family, dtype == MC_F64);
-  hipError_t e = ops->eval_cond(p->dev, n, q, ld, lambda, kappa, static_cast<hipStream_t>(stream));
-  if (e != hipSuccess) return hip_fail(e, "mc_eval_condition: launch");
-  return MC_OK;
+  return eval_condition("mc_eval_condition", p, n, q, ld, dtype, lambda, 0, kappa, stream);
+}
+
+mc_status mc_eval_step_condition(const mc_problem* p, int64_t n, const void* q, int64_t ld, mc_dtype dtype, double lambda,
+                                 void* kappa, void* stream) {
+  return eval_condition("mc_eval_step_condition", p, n, q, ld, dtype, lambda, 1, kappa, stream);
 }
 
 mc_status mc_set_check_lanes(mc_problem* p, int32_t lanes) {

@@ -1258,30 +1258,29 @@ __global__ void __launch_bounds__(256) k_eval_fj(const DevProblem* Pp, int64_t n
   }
 }
 
-// Diagnostic: the condition estimate (max L_ii / min L_ii)^2 of J J^T + lambda I as the step
-// computes it in precision S (+inf where the factorisation fails). The iterate is staged in LDS
-// as in the projection kernels. Dynamic LDS: D * blockDim doubles.
-template <class Model, class IO, class S>
+// Diagnostic: the condition estimate (max L_ii / min L_ii)^2 of J J^T + lambda I in precision S (+inf where the
+// factorisation fails), in the rows of the passes W: the scene's own (Direct) or the projection kernels' (StepOf).
+// Dynamic LDS: the sine table, D * blockDim doubles (iterates).
+template <class Model, class IO, class S, class W>
 __global__ void __launch_bounds__(64) k_eval_cond(const DevProblem* Pp, int64_t n, const void* qv, int64_t ld,
                                                   double lambda, void* kappa_out) {
   constexpr int D = Model::D, M = Model::M;
   extern __shared__ double smem[];
   const Consts& C = consts_of(Pp);
+  const auto tr = make_trig<Model, false>(smem, nullptr);
   const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
   if (i >= n) return;
   const int dof = dof_of<Model>(C);
-  const QLds q = q_lds<D>(smem);
+  const QLds q = q_lds<D>(smem + kTabDoubles<Model>);
   const IO* p = static_cast<const IO*>(qv) + i;
   for (int c = 0; c < D; ++c) q.set(c, c < dof ? double(p[int64_t(c) * ld]) : 0.0);
-  typename Model::template SD<S> sd;
+  typename W::template SD<S> sd;
   S F[M], G[M * (M + 1) / 2], invd[M], kappa;
-  Model::template residual<S>(q, C, F, sd);
-  Model::template gram<S, false>(q, C, sd, G, nullptr, nullptr);
+  W::template residual<S>(q, C, F, sd, tr);
+  W::template gram<S>(q, C, sd, tr, G);
+  if (lambda > 0.0) W::template add_lambda<S>(G, F, S(lambda), tr);
   S maxd = S(0);
-  for (int r = 0; r < M; ++r) {
-    G[pidx(r, r)] += S(lambda);
-    maxd = G[pidx(r, r)] > maxd ? G[pidx(r, r)] : maxd;
-  }
+  for (int r = 0; r < M; ++r) maxd = G[pidx(r, r)] > maxd ? G[pidx(r, r)] : maxd;
   const S floor = std::is_same<S, float>::value ? S(kFloorF32) : S(kFloorF64);
   const bool ok = cholesky<Model, S>(G, invd, kappa, floor * maxd, drop_bits<Model>(sd));
   st_io<IO>(kappa_out, i, ok ? double(kappa) : __builtin_huge_val());

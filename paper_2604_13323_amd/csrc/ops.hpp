@@ -26,8 +26,8 @@ struct FamilyOps {
   hipError_t (*vjp_tail)(const VjpArgs& a, int grid, hipStream_t s);  // FP32 mode only
   hipError_t (*vjp_exact)(const VjpxArgs& a, hipStream_t s);
   hipError_t (*eval_fj)(const DevProblem* P, int64_t n, const void* q, int64_t ld, void* F, void* J, hipStream_t s);
-  hipError_t (*eval_cond)(const DevProblem* P, int64_t n, const void* q, int64_t ld, double lambda, void* kappa,
-                          hipStream_t s);
+  hipError_t (*eval_cond)(const DevProblem* P, int64_t n, const void* q, int64_t ld, double lambda, int step_rows,
+                          void* kappa, hipStream_t s);
   // of the persistent kernel's build for a mode (STACKED, CYCLIC, OUTER)
   int (*persistent_blocks_per_cu)(int block, int mode);
   size_t (*lds_bytes)(int block, int mode);  // dynamic LDS
@@ -65,8 +65,8 @@ struct OpsImpl {
   static hipError_t vjp(const VjpArgs& a, hipStream_t s);
   static hipError_t vjp_exact(const VjpxArgs& a, hipStream_t s);
   static hipError_t eval_fj(const DevProblem* P, int64_t n, const void* q, int64_t ld, void* F, void* J, hipStream_t s);
-  static hipError_t eval_cond(const DevProblem* P, int64_t n, const void* q, int64_t ld, double lambda, void* kappa,
-                              hipStream_t s);
+  static hipError_t eval_cond(const DevProblem* P, int64_t n, const void* q, int64_t ld, double lambda, int step_rows,
+                              void* kappa, hipStream_t s);
   static constexpr bool kF32 = std::is_same<S, float>::value;
   static FamilyOps make() {
     FamilyOps o;

@@ -138,9 +138,12 @@ hipError_t OpsImpl<Model, IO, S>::eval_fj(const DevProblem* P, int64_t n, const 
 }
 template <class Model, class IO, class S>
 hipError_t OpsImpl<Model, IO, S>::eval_cond(const DevProblem* P, int64_t n, const void* q, int64_t ld, double lambda,
-                                            void* kappa, hipStream_t s) {
-  hipLaunchKernelGGL((k_eval_cond<Model, IO, S>), dim3(blocks_for(n, 64)), dim3(64), tile_bytes(64), s, P, n, q, ld,
-                     lambda, kappa);
+                                            int step_rows, void* kappa, hipStream_t s) {
+  using W = typename StepOf<Model>::type;
+  const dim3 g(blocks_for(n, 64)), b(64);
+  const size_t lds = 8 * size_t(kTabDoubles<Model>) + tile_bytes(64);
+  if (step_rows) hipLaunchKernelGGL((k_eval_cond<Model, IO, S, W>), g, b, lds, s, P, n, q, ld, lambda, kappa);
+  else hipLaunchKernelGGL((k_eval_cond<Model, IO, S, Direct<Model>>), g, b, lds, s, P, n, q, ld, lambda, kappa);
   return hipGetLastError();
 }
 }  // namespace mc
@@ -165,7 +168,7 @@ hipError_t OpsImpl<Model, IO, S>::eval_cond(const DevProblem* P, int64_t n, cons
 #define MC_INST_VJP_EXACT(O) template hipError_t O::vjp_exact(const mc::VjpxArgs&, hipStream_t);
 #define MC_INST_DIAG(O)                                                                              \
   template hipError_t O::eval_fj(const mc::DevProblem*, int64_t, const void*, int64_t, void*, void*, hipStream_t); \
-  template hipError_t O::eval_cond(const mc::DevProblem*, int64_t, const void*, int64_t, double, void*, hipStream_t);
+  template hipError_t O::eval_cond(const mc::DevProblem*, int64_t, const void*, int64_t, double, int, void*, hipStream_t);
 // every launcher a single-block family uses (its cyclic mode is the stacked one), in one unit
 #define MC_INST_LIGHT_F32(O) MC_INST_PERSISTENT(O) MC_INST_PLAIN(O) MC_INST_TAIL(O) MC_INST_CHECK(O) \
   MC_INST_VJP(O) MC_INST_VJP_TAIL(O) MC_INST_VJP_EXACT(O) MC_INST_DIAG(O)
