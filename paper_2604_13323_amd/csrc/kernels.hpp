@@ -417,13 +417,13 @@ __device__ __forceinline__ int finish_fp64(const QLds& q, const QLds& q0, const 
 // cosines (TILE; two floats per entry).
 template <class Model>
 constexpr int kTabDoubles = StepOf<Model>::type::trig ? kSinTabDoubles : 0;
-template <class Model, bool TILE>
-using TrigFor = std::conditional_t<!StepOf<Model>::type::trig, TrigNone, std::conditional_t<TILE, TrigTile, TrigLive>>;
+template <class Model, bool TILE, bool EXACT = true>
+using TrigFor = std::conditional_t<!StepOf<Model>::type::trig, TrigNone, std::conditional_t<TILE, TrigTile, TrigLiveOf<EXACT>>>;
 // The lane's trig source; tile: the kernel's first double of trig tiles. The table is staged by the whole
 // block, before any lane leaves.
-template <class Model, bool TILE>
-__device__ __forceinline__ TrigFor<Model, TILE> make_trig(double* smem, double* tile) {
-  TrigFor<Model, TILE> t;
+template <class Model, bool TILE, bool EXACT = true>
+__device__ __forceinline__ TrigFor<Model, TILE, EXACT> make_trig(double* smem, double* tile) {
+  TrigFor<Model, TILE, EXACT> t;
   if constexpr (StepOf<Model>::type::trig) {
     stage_sin_tab(smem);
     __syncthreads();
@@ -1147,7 +1147,8 @@ __global__ void __launch_bounds__(64) k_vjp_exact(VjpxArgs a) {
   using W = typename StepOf<Model>::type;
   extern __shared__ double smem[];
   const Consts& C = consts_of(a.P);
-  const auto tr = make_trig<Model, false>(smem, nullptr);
+  // (FP32 gradients: the sines' last bit moves the differences below by 1e-12 of themselves, and costs 5 % of the kernel)
+  const auto tr = make_trig<Model, false, std::is_same<IO, double>::value>(smem, nullptr);
   const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
   if (i >= a.n) return;
   const int dof = dof_of<Model>(C);

@@ -238,7 +238,7 @@ struct Leaf {
       sfor<0, List::N>([&](auto I) {
         constexpr int i = decltype(I)::value;
         double s, c;
-        sincos_tab(x[i], tr.tab, s, c);
+        sincos_tab<std::is_same<S, double>::value && TR::exact>(x[i], tr.tab, s, c);
         d[i].q = S(x[i]);
         d[i].s = S(s);
         d[i].c = S(c);
@@ -382,7 +382,7 @@ struct Leaf {
           if constexpr (TR::tile) tr.set(j, float(x[g][k]), 0.f);
         } else {
           double sn, cs;
-          sincos_finish(x[g][k], kr[g][k], t[g][k], sn, cs);
+          sincos_finish<std::is_same<T, double>::value && TR::exact>(x[g][k], kr[g][k], t[g][k], sn, cs);
           d[g][k].s = T(sn);
           d[g][k].c = T(cs);
           if constexpr (TR::tile) tr.set(j, float(sn), float(cs));

@@ -89,6 +89,7 @@ using SinTabP = const __attribute__((address_space(3))) double*;
 // the reduction to pi/4 with its series to r^15 and r^16. Root mean square error over +-20 rad 2.7e-17, largest relative
 // error 1.9e-16 (that of the series 3.2e-17 and 2.1e-16; without el and lo, 18 operations, 4.6e-17 and 3.5e-16).
 // In two parts, so that other work can stand between the reads and their use: the entry (and k), then the rest.
+// EXACT = false, for values that are rounded to FP32 at once: without el and lo, and one read.
 using SinTabV = double __attribute__((ext_vector_type(2)));
 struct SinTabE {
   SinTabV v, lo;
@@ -105,39 +106,48 @@ __device__ __forceinline__ SinTabE sin_tab_entry(double x, SinTabP tab, double& 
   const SinTabP p = tab + 4 * sin_tab_index(x, k);
   return SinTabE{*(P)p, *(P)(p + 2)};
 }
+template <bool EXACT = true>
 __host__ __device__ __forceinline__ void sincos_finish(double x, double k, const SinTabE& t, double& s, double& c) {
   const double r0 = __builtin_fma(-k, 0.09817477042468103, x);
   const double el = -k * 3.827021247335479e-18;
-  const double r = r0 + el;
+  const double r = EXACT ? r0 + el : __builtin_fma(-k, 3.827021247335479e-18, r0);
   const double r2 = r * r;
   double ps = __builtin_fma(r2, -0.00019840273844900185, 0.008333333324333671);
   double pc = __builtin_fma(r2, 1.0 / 40320.0, -1.0 / 720.0);
   ps = __builtin_fma(r2, ps, -0.16666666666666546);
   pc = __builtin_fma(r2, pc, 1.0 / 24.0);
-  const double sr = __builtin_fma(r * r2, ps, el);  // sin r - r0
+  const double sr = __builtin_fma(r * r2, ps, EXACT ? el : r);  // sin r - r0, or sin r
   pc = __builtin_fma(r2, pc, -0.5);
   const double cm = r2 * pc;
+  if constexpr (!EXACT) {
+    s = __builtin_fma(t.v.y, sr, __builtin_fma(t.v.x, cm, t.v.x));
+    c = __builtin_fma(-t.v.x, sr, __builtin_fma(t.v.y, cm, t.v.y));
+    return;
+  }
   s = t.v.x + __builtin_fma(t.v.y, r0, __builtin_fma(t.v.y, sr, __builtin_fma(t.v.x, cm, t.lo.x)));
   c = t.v.y + __builtin_fma(-t.v.x, r0, __builtin_fma(-t.v.x, sr, __builtin_fma(t.v.y, cm, t.lo.y)));
 }
+template <bool EXACT = true>
 __device__ __forceinline__ void sincos_tab(double x, SinTabP tab, double& s, double& c) {
   double k;
   const SinTabE t = sin_tab_entry(x, tab, k);
-  sincos_finish(x, k, t, s, c);
+  sincos_finish<EXACT>(x, k, t, s, c);
 }
 
-// Where the walks take sines and cosines from. TrigLive: computed from the iterate in every pass.
+// Where the walks take sines and cosines from. TrigLive: computed from the iterate in every pass (EXACT: the FP64 passes').
 // TrigTile: the residual pass stores them, rounded to FP32, in a per-lane column of a [D][64] LDS tile
 // (a prismatic joint's slot holds its coordinate) and the FP32 step passes read them there.
 // fresh(): the same source for another pass, whose reads the compiler cannot merge with an earlier pass's (it would
 // keep every value in registers in between).
-struct TrigLive {
-  static constexpr bool tile = false;
+template <bool EXACT>
+struct TrigLiveOf {
+  static constexpr bool tile = false, exact = EXACT;
   SinTabP tab;
-  __device__ __forceinline__ TrigLive fresh() const { return *this; }
+  __device__ __forceinline__ TrigLiveOf fresh() const { return *this; }
 };
+using TrigLive = TrigLiveOf<true>;
 struct TrigTile {
-  static constexpr bool tile = true;
+  static constexpr bool tile = true, exact = true;
   using V2 = float __attribute__((ext_vector_type(2)));
   using LP = __attribute__((address_space(3))) V2*;
   SinTabP tab;
