@@ -260,7 +260,7 @@ __device__ __forceinline__ const float4* obs_of(const DevProblem* P) {
   OT* oc = (OT*)uniform_ptr(o);
   return (const float4*)oc;
 }
-// The obstacle slots of the clusters, kClusterSize each, as scalar-load memory.
+// The obstacle slots of the clusters, kClusterSize each (a generic pointer where it is used: vector loads).
 __device__ __forceinline__ const float4* obs_pad_of(const DevProblem* P) {
   using PT = const float4* const __attribute__((address_space(4)));
   const float4* o = *(PT*)uniform_ptr(&P->obs_pad);

@@ -2,8 +2,8 @@
 //
 // Mapping: one configuration per lane; the lane's FP64 iterate lives in LDS (a column
 // of a [D][blockDim] array, conflict-free); the kinematic constants are read with scalar
-// loads (wave-uniform, so they occupy scalar registers), as is the scene in the exact check;
-// everything else is in registers. The hot
+// loads (wave-uniform, so they occupy scalar registers), as are the boxes of the scene in the exact
+// check; everything else is in registers. The hot
 // loop (Alg. 2 ParallelProject with getDescentStep on one stacked block) per iteration:
 //   1. residual pass, FP64: forward kinematics, F(q), ||F||^2, and the per-block data
 //      the Jacobian columns need;
@@ -606,14 +606,14 @@ k_project_persistent(ProjArgs) {
 }
 
 // Exact collision check of the configurations queued by k_project_persistent: one configuration per lane, a work item per
-// 64 queued configurations and link (grid-stride). A lane group per configuration walked the whole tree in every lane of
-// the group and its wave ran the union of its groups' pair lists, every box and obstacle a vector operand; here a link's
-// chain is walked once per configuration and the scene is read into scalar registers. Bound by instruction issue where
-// most clusters are near, by the latency of the scalar reads else (four waves per SIMD: a chain's
-// coordinates, read at once, take 107 registers; five or more spill).
-// Before (groups of 4 lanes) and after, us: 65,536 humanoid configurations 26.5 -> 17.0, Digit 149 -> 107, 65,536 checked
-// humanoid configurations near the shelves 156 -> 106, 4,000 dual-arm geodesics of 4 to 128 configurations 349 -> 89,
-// 131,072 arm configurations 114 -> 17, 1,021 arm geodesics of 4 to 64 configurations 79 -> 30.
+// 64 queued configurations, link and share of the clusters (grid-stride). A lane group per configuration walked the whole
+// tree in every lane of the group and its wave ran the union of its groups' pair lists; here a link's chain is walked once
+// per configuration, the boxes come by 64-byte scalar reads and a cluster's sixteen obstacles by vector reads of one address
+// (64 of the 108 registers). Bound by instruction issue where most clusters are near, by the latency of those reads
+// else: they stand before the sphere tests, so a cluster that no sphere reaches pays for them too.
+// Before (groups of 4 lanes) and after, us: 65,536 humanoid configurations 26.5 -> 14.5, Digit 149 -> 98, 65,536 checked
+// humanoid configurations near the shelves 156 -> 99, 4,000 dual-arm geodesics of 4 to 128 configurations 349 -> 86,
+// 131,072 arm configurations 114 -> 17.2, 1,021 arm geodesics of 4 to 64 configurations 79 -> 31.
 template <class Model>
 __global__ void __launch_bounds__(256, 4) k_check_lanes(ProjArgs a) {
   __shared__ float4 slot_mem[4 * 64];  // launched with 256 threads
@@ -659,7 +659,7 @@ __global__ void __launch_bounds__(256, 4) k_check_lanes(ProjArgs a) {
 }
 
 // The same check with groups of L lanes per configuration: the autotuner's alternatives on long queues (chk_long, 2
-// to 16 lanes), and what a caller may force (chk_lanes, 2 to 64).
+// to 16 lanes), what a caller may force (chk_lanes, 2 to 64), and the launcher's choice where many obstacles are near.
 // Every lane of a group walks the tree, and the group splits the sphere-obstacle tests of
 // the (link, cluster) pairs it finds overlapping: smaller groups repeat fewer walks, but the lanes of
 // a wave then run different pair lists and the wave runs their union, so the best size depends on

@@ -1195,7 +1195,9 @@ struct Kin {
   // Gathering pays where obstacles are scattered among an arm's links, so that a cluster's box says little (check of 4,000
   // dual-arm geodesics 197 -> 89 us, of 131,072 arm configurations 55 -> 17, of 1,021 arm geodesics 36 -> 30). The links of the
   // 36-DoF trees meet packed slabs, whose clusters are compact and of which more than 64 obstacles are in reach at once:
-  // there it costs (Digit 107 -> 114 us, configurations near the shelves 106 -> 115).
+  // there it costs (Digit 107 -> 114 us, configurations near the shelves 106 -> 115). The line is the families' dimension, a
+  // proxy: an arm among packed slabs tries it and falls back (65,536 arm configurations among 200 or 2,000 slab spheres 46 to 143
+  // us, groups of 4 lanes 50 to 156); trees among scattered obstacles are not built with it.
   static constexpr int kGatherMaxD = 16;
   // The obstacles within reach of the wave's copies of a link's bound (centre cb, radius r) into the wave's 64 LDS slots:
   // the lanes test 64 cluster boxes at once against the ball around them, then the obstacles of four near clusters.
@@ -1263,9 +1265,9 @@ struct Kin {
   // wave-uniform. Arms (kGatherMaxD): where the wave's copies of the link are close together (neighbouring configurations
   // of a geodesic), few obstacles are within reach of any of them, and gather() finds those with a lane per obstacle. Else,
   // and where that gives more than 64, the link's bound is tested lane by lane against the boxes of the cluster groups
-  // and of their clusters, four boxes per scalar read, and a cluster that any lane's link reaches is taken for the whole
-  // wave, its box and all its obstacles read at once into scalar registers and tested against the link's spheres four at
-  // a time. Lanes that did not need a test run it all the same: an overlap it finds is one.
+  // and of their clusters, four boxes at a time by scalar reads, and a cluster that any lane's link reaches is taken for the
+  // whole wave, its obstacles read at once (vector reads of one address: pad is a generic pointer) and tested against the
+  // link's spheres four at a time. Lanes that did not need a test run it all the same: an overlap it finds is one.
   // part: of every 64 clusters, those to test.
   static __device__ __forceinline__ bool link_hits(const Rig<float>& X, int l, const CollConsts& K, const float4* pad, bool live,
                                                    float4* slots, uint64_t part) {
