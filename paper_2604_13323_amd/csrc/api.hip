@@ -1804,17 +1804,17 @@ mc_status extend_batch(const mc_problem* p, int64_t E, const void* q_start, cons
 static mc_status eval_condition(const char* who, const mc_problem* p, int64_t n, const void* q, int64_t ld, mc_dtype dtype,
                                 double lambda, int step_rows, void* kappa, void* stream) {
   g_err.clear();
-  const std::string w(who);
-  if (!p) return fail(MC_ERR_INVALID_ARG, w + ": null problem");
-  if (n < 0) return fail(MC_ERR_INVALID_ARG, w + ": n < 0");
-  if (dtype != MC_F32 && dtype != MC_F64) return fail(MC_ERR_INVALID_ARG, w + ": bad dtype");
-  if (!(lambda >= 0) || !std::isfinite(lambda)) return fail(MC_ERR_INVALID_ARG, w + ": lambda must be >= 0");
+  auto bad = [&](const char* what) { return fail(MC_ERR_INVALID_ARG, std::string(who) + what); };
+  if (!p) return bad(": null problem");
+  if (n < 0) return bad(": n < 0");
+  if (dtype != MC_F32 && dtype != MC_F64) return bad(": bad dtype");
+  if (!(lambda >= 0) || !std::isfinite(lambda)) return bad(": lambda must be >= 0");
   if (n == 0) return MC_OK;
-  if (!q || !kappa) return fail(MC_ERR_INVALID_ARG, w + ": null array");
-  if (ld < n) return fail(MC_ERR_INVALID_ARG, w + ": ld < n");
+  if (!q || !kappa) return bad(": null array");
+  if (ld < n) return bad(": ld < n");
   const FamilyOps* ops = ops_for(p->family, dtype == MC_F64);
   hipError_t e = ops->eval_cond(p->dev, n, q, ld, lambda, step_rows, kappa, static_cast<hipStream_t>(stream));
-  if (e != hipSuccess) return hip_fail(e, (w + ": launch").c_str());
+  if (e != hipSuccess) return hip_fail(e, (std::string(who) + ": launch").c_str());
   return MC_OK;
 }
 
